@@ -2387,13 +2387,10 @@ ah_status ah_amplicon_fasta(const ah_genomes* g, const ah_hit* d_hits, const ah_
   uint32_t* rec_len = c.take<uint32_t>(amp_capacity ? amp_capacity : 1);
   uint64_t* rec_at = c.take<uint64_t>(amp_capacity ? amp_capacity : 1);
   uint64_t* cc = c.take<uint64_t>(ah::kPairGrid);
-  // writers: up to 32 waves per CU, no more than the amplicons can use
-  const uint64_t waves = std::min<uint64_t>(std::max<uint64_t>(amp_capacity, 1),
-                                            (uint64_t)cu_count() * 32u);
   ProfScope prof("fasta", (hipStream_t)stream);
   AH_HIP(ah::launch_fasta(*g, d_hits, d_amp, d_namp, amp_capacity, n_pairs, d_text, text_capacity,
                           d_text_res, d_seq_hash, d_amplitype, d_amplitype_n, rec_len, rec_at, cc,
-                          (int)waves, (hipStream_t)stream));
+                          cu_count(), (hipStream_t)stream));
   return AH_OK;
 }
 

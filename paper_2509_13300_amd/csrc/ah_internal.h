@@ -156,12 +156,12 @@ hipError_t launch_seg_tail(ah_hit* staged, ah_hit* out, uint64_t hcap, const Seg
                            ah_result* ares, bool exact, hipStream_t st);
 
 // Amplicon FASTA records, sequence hashes and amplitypes (see ah.h); rec_len
-// [acap], rec_at [acap] and cc [kPairGrid] are workspace; `waves` writers.
+// [acap], rec_at [acap] and cc [kPairGrid] are workspace; cus: compute units.
 hipError_t launch_fasta(const ah_genomes& g, const ah_hit* hits, const ah_amplicon* amp,
                         const ah_result* namp, uint64_t acap, uint32_t n_pairs, char* text,
                         uint64_t tcap, ah_result* res, uint64_t* seq_hash, uint64_t* atype,
                         uint32_t* atype_n, uint32_t* rec_len, uint64_t* rec_at, uint64_t* cc,
-                        int waves, hipStream_t st);
+                        int cus, hipStream_t st);
 
 // Streaming: word offsets of genomes off[0..n] relative to off[0], and the
 // chunk-local -> collection id fix-up of a chunk's hits and amplicons.

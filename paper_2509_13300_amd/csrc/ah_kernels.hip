@@ -4,6 +4,7 @@
 // run time (scan_core.hip).
 #include <math.h>
 
+#include <algorithm>
 #include <mutex>
 
 #include "ah_internal.h"
@@ -1910,26 +1911,8 @@ __device__ __forceinline__ u64 mix64(u64 z) {
 }
 
 __device__ __forceinline__ u32 dec_digits(u32 v) {
-  u32 d = 1;
-  while (v >= 10u) {
-    v /= 10u;
-    ++d;
-  }
-  return d;
-}
-
-__device__ __forceinline__ char* put_dec(char* o, u32 v) {
-  const u32 d = dec_digits(v);
-  for (u32 i = d; i > 0; --i) {
-    o[i - 1] = (char)('0' + v % 10u);
-    v /= 10u;
-  }
-  return o + d;
-}
-
-__device__ __forceinline__ char* put_str(char* o, const char* s) {
-  while (*s) *o++ = *s++;
-  return o;
+  return 1u + (v >= 10u) + (v >= 100u) + (v >= 1000u) + (v >= 10000u) + (v >= 100000u) +
+         (v >= 1000000u) + (v >= 10000000u) + (v >= 100000000u) + (v >= 1000000000u);
 }
 
 // Tm x 100 rounded half to even, as a magnitude and a sign; false for NaN.
@@ -1947,18 +1930,6 @@ __device__ __forceinline__ u32 tm_len(float v) {
   bool neg;
   if (!tm_centi(v, a, neg)) return 3;  // "nan"
   return (neg ? 1u : 0u) + dec_digits(a / 100u) + 3u;
-}
-
-__device__ __forceinline__ char* put_tm(char* o, float v) {
-  u32 a;
-  bool neg;
-  if (!tm_centi(v, a, neg)) return put_str(o, "nan");
-  if (neg) *o++ = '-';
-  o = put_dec(o, a / 100u);
-  *o++ = '.';
-  *o++ = (char)('0' + (a % 100u) / 10u);
-  *o++ = (char)('0' + a % 10u);
-  return o;
 }
 
 __device__ __forceinline__ u32 fasta_header_len(const ah_amplicon& A, const ah_hit* hits) {
@@ -2022,27 +1993,234 @@ __global__ __launch_bounds__(kBlock) void k_fasta_offsets(
   }
 }
 
-// 3: one wave per amplicon (grid-stride): lane 0 writes the header, the
-// lanes the bases (lane j takes bases j, j + 64, ...: its word index steps by
-// 64 words, wrapping into the next segment, with no division per base), and
-// the wave sums the lanes' shares of the sequence hash.
-__global__ __launch_bounds__(kBlock) void k_fasta_write(
+// Character `pos` of the header of amplicon A, whose sites' Tm are tp and tm:
+// the fields are walked in order, and the one that holds the character
+// leaves its number and the digit's weight, or the character itself.
+__device__ __forceinline__ char fasta_header_char(const ah_amplicon& A, float tp, float tm,
+                                                  u32 pos, const u32* pow10) {
+  u32 v = 0, e = 0, at = 0;
+  char ch = 0;
+  auto lit = [&](u64 text, u32 len) {  // up to 8 characters, the first in the low byte
+    if (pos - at < len) ch = (char)(text >> (8u * (pos - at)));
+    at += len;
+  };
+  auto num = [&](u32 x, u32 digits) {
+    if (pos - at < digits) {
+      v = x;
+      e = digits - 1u - (pos - at);
+    }
+    at += digits;
+  };
+  auto deg = [&](float x) {
+    u32 a;
+    bool neg;
+    if (!tm_centi(x, a, neg)) {
+      lit('n' | 'a' << 8 | 'n' << 16, 3);
+      return;
+    }
+    if (neg) lit('-', 1);
+    num(a / 100u, dec_digits(a / 100u));
+    lit('.', 1);
+    num(a % 100u, 2);
+  };
+  lit('>' | 'g' << 8, 2);
+  num(A.genome, dec_digits(A.genome));
+  lit(':', 1);
+  num(A.start, dec_digits(A.start));
+  lit('-', 1);
+  num(A.end, dec_digits(A.end));
+  lit(0x3d7269617020ull, 6);    // " pair="
+  num(A.pair, dec_digits(A.pair));
+  lit(0x3d746e6569726f20ull, 8);  // " orient="
+  const bool f1 = A.orient == AH_FR || A.orient == AH_FF, f2 = A.orient == AH_RF || A.orient == AH_FF;
+  lit((f1 ? 'F' : 'R') | (f2 ? 'F' : 'R') << 8, 2);
+  lit(0x3d6d7420ull, 4);        // " tm="
+  deg(tp);
+  lit(',', 1);
+  deg(tm);
+  lit('\n', 1);
+  return ch ? ch : (char)('0' + v / pow10[e] % 10u);
+}
+
+__device__ __forceinline__ u64 pow_p(u32 e) {  // kSeqP^e mod 2^64
+  u64 r = 1, q = kSeqP;
+  for (; e; e >>= 1, q *= q)
+    if (e & 1u) r *= q;
+  return r;
+}
+
+// 3: a wave per amplicon.  The lanes write the header, a character each.  Of
+// the sequence a lane takes eight consecutive bases at a time, the wave 512: it
+// reads the eight words that hold them (64 bytes; a segment's words run on into
+// the next segment's first words, so the bit stays the same), picks out the
+// codes side by side in two registers and writes eight letters at once.  The
+// sequence hash is a polynomial; four bases' share comes from a table of the
+// 256 code combinations, and the steps are walked from the last to the first,
+// so that one multiplication (Horner) takes a step.
+//
+// A base costs 8 bytes of words for 1 byte written, since 32 segments share a
+// word, and the amplicons of one genome reuse its words.  So the grid is what
+// is resident at once (few genomes in work), and each XCD takes a run of
+// consecutive amplicons: their words come from its L2 (HBM reads are the
+// genomes once, 261 MB for 250 of them).  What bounds it then is the vector
+// ALU (57% of its cycles) and the L1, which a lane's 64 contiguous bytes cross
+// 16 at a time.
+// Measured on amplicons of 3.7 kb from 250 genomes (133 MB of text), cold caches:
+// 0.19 ms for the call (0.63 ms with a lane per base, a wave per amplicon over
+// the whole grid, two 64-bit multiplications a base and the header by one lane;
+// four bases a lane 0.27; the waves of a workgroup sharing a sequence 0.22; 3, 5
+// and 6 workgroups a CU 0.22, 0.20, 0.21).
+constexpr u32 kFastaStep = 512;  // bases a wave takes at a time, 8 a lane
+constexpr int kFastaBlocks = 4;  // workgroups per CU
+
+// What a wave reads of an amplicon.
+struct FastaSeq {
+  const uint2* w;   // the genome's words
+  const u32* nm;    // its mask words, or null
+  char* out;        // the first letter; null when the record does not fit
+  u64 start, end;
+  u32 S, len;
+  bool rc;
+};
+
+// Codes of the bases at bit b of words v[0..3], one a byte, in order.
+__device__ __forceinline__ u32 fasta_codes(const uint2* v, u32 b) {
+  // the byte of each word that holds bit b, side by side, then the bit of each
+  const u32 sel = (b >> 3) * 0x0101u + 0x0400u, sh = b & 7u;
+  const u32 x = __builtin_amdgcn_perm(__builtin_amdgcn_perm(v[3].x, v[2].x, sel),
+                                      __builtin_amdgcn_perm(v[1].x, v[0].x, sel), 0x05040100u);
+  const u32 y = __builtin_amdgcn_perm(__builtin_amdgcn_perm(v[3].y, v[2].y, sel),
+                                      __builtin_amdgcn_perm(v[1].y, v[0].y, sel), 0x05040100u);
+  return (((x >> sh) & 0x01010101u) << 1) | ((y >> sh) & 0x01010101u);
+}
+
+// Letters of one lane's m bases (at most 8), at word t and bit b of the genome
+// (rc: the last of them is there), written to o (not null); returns their share
+// of the hash, sum (c_j + 1) P^j.
+__device__ __forceinline__ u64 fasta_lane(const FastaSeq& F, int t, u32 b, u32 m, char* o,
+                                          const u64 (*s_hash)[256]) {
+  uint2 v[8];
+  __builtin_memcpy(v, F.w + t, 64);  // a segment's words and the halo after it
+  u32 s0 = fasta_codes(v, b), s1 = fasta_codes(v + 4, b);
+  u32 n0 = 0, n1 = 0;  // bit 8 j: base j is not A/C/G/T
+  if (F.nm) {
+    u32 nv[8];
+    __builtin_memcpy(nv, F.nm + t, 32);
+#pragma unroll
+    for (u32 e = 0; e < 4; ++e) {
+      n0 |= ((nv[e] >> b) & 1u) << (8u * e);
+      n1 |= ((nv[e + 4] >> b) & 1u) << (8u * e);
+    }
+  }
+  if (F.rc) {  // complement, and the order turned round (m bases from the far end)
+    const u32 c = 0x03030303u, turn = 0x00010203u;
+    u64 s = ((u64)__builtin_amdgcn_perm(0u, s0 ^ c, turn) << 32) | __builtin_amdgcn_perm(0u, s1 ^ c, turn);
+    s >>= 8u * (8u - m);
+    s0 = (u32)s;
+    s1 = (u32)(s >> 32);
+    if (F.nm) {
+      s = ((u64)__builtin_amdgcn_perm(0u, n0, turn) << 32) | __builtin_amdgcn_perm(0u, n1, turn);
+      s >>= 8u * (8u - m);
+      n0 = (u32)s;
+      n1 = (u32)(s >> 32);
+    }
+  }
+  u64 h;
+  if (m < 8u || (n0 | n1) != 0u) {  // bases that are not there, or not A/C/G/T
+    u64 pj = 1;
+    h = 0;
+    s0 = (s0 & ~(n0 * 3u)) | (n0 << 2);  // code 4: N
+    s1 = (s1 & ~(n1 * 3u)) | (n1 << 2);
+    for (u32 j = 0; j < m; ++j, pj *= kSeqP)
+      h += (u64)((((j < 4u ? s0 : s1) >> (8u * (j & 3u))) & 0xffu) + 1u) * pj;
+  } else {
+    const u32 a = s0 | (s0 >> 6), c = s1 | (s1 >> 6);
+    h = s_hash[0][(a | (a >> 12)) & 0xffu] + s_hash[1][(c | (c >> 12)) & 0xffu];
+  }
+  if (o) {
+    const u32 l[2] = {__builtin_amdgcn_perm('N', 0x54474341u, s0),   // A C G T, N
+                      __builtin_amdgcn_perm('N', 0x54474341u, s1)};
+    if (m == 8u) {
+      __builtin_memcpy(o, l, 8);
+    } else {
+      for (u32 j = 0; j < m; ++j) o[j] = (char)(l[j >> 2] >> (8u * (j & 3u)));
+    }
+  }
+  return h;
+}
+
+// Letters and hash share of a sequence (this lane's part of the sum), steps of
+// 512 bases, the last one first (only that can be partial).
+__device__ __forceinline__ u64 fasta_sequence(const FastaSeq& F, u32 lane,
+                                              const u64 (*s_hash)[256], u64 Q) {
+  if (F.len == 0) return 0;
+  const int S = (int)F.S;  // <= 2^27
+  // this lane's bases are k .. k + 7 of the record, at genome positions b * S +
+  // t .. + 7 (rc: in reverse); before the genome's start b is 0 and t negative
+  u32 i = (F.len - 1u) / kFastaStep, k = i * kFastaStep + 8u * lane;
+  const long long q0 = F.rc ? (long long)F.end - 8 - (long long)k : (long long)F.start + (long long)k;
+  u32 b = 0;
+  int t = (int)q0;
+  if (q0 >= S) {
+    b = q0 <= 0xffffffffll ? (u32)q0 / F.S : (u32)(q0 / S);
+    t = (int)(q0 - (long long)b * S);
+  }
+  const u32 m = k < F.len ? min(F.len - k, 8u) : 0u;
+  u64 acc = 0;
+  // rc: the bases of a partial lane end at the amplicon's start
+  if (m) acc = fasta_lane(F, F.rc ? t + (int)(8u - m) : t, b, m, F.out ? F.out + k : nullptr, s_hash);
+  for (; i > 0; --i) {
+    k -= kFastaStep;
+    if (F.rc) {
+      t += (int)kFastaStep;
+      while (t >= S) {
+        t -= S;
+        ++b;
+      }
+    } else {
+      t -= (int)kFastaStep;
+      while (t < 0) {
+        t += S;
+        --b;
+      }
+    }
+    acc = acc * Q + fasta_lane(F, t, b, 8u, F.out ? F.out + k : nullptr, s_hash);
+  }
+  return acc;
+}
+
+__global__ __launch_bounds__(kBlock, kFastaBlocks) void k_fasta_write(
     const uint2* __restrict__ words, const u32* __restrict__ nmask, const u64* __restrict__ word_off,
     const u32* __restrict__ glen, u32 n_genomes, const ah_amplicon* __restrict__ amp,
     const ah_result* __restrict__ namp, u64 acap, const ah_hit* __restrict__ hits,
     const u32* __restrict__ rec_len, const u64* __restrict__ rec_at, char* __restrict__ text,
     u64 tcap, u64* __restrict__ seq_hash, u64* __restrict__ atype, u32* __restrict__ atype_n,
     u32 n_pairs) {
-  const u64 n = pair_n(namp, acap);
+  // [0]: sum over j < 4 of (c_j + 1) P^j, c_j = bits 2j of the index; [1]: times P^4
+  __shared__ u64 s_hash[2][256];
+  __shared__ u32 s_pow10[10];
+  constexpr u64 P1 = kSeqP, P2 = P1 * P1, P3 = P2 * P1;
   const u32 lane = threadIdx.x & 63u;
-  const u64 wid = ((u64)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
-  const u64 nw = ((u64)gridDim.x * blockDim.x) >> 6;
-  // P^lane and Q = P^64 for the lane-parallel sequence hash
-  u64 p_lane = 1;
-  for (u32 e = 0; e < lane; ++e) p_lane *= kSeqP;
-  u64 Q = kSeqP;
-  for (int e = 0; e < 6; ++e) Q *= Q;
-  for (u64 ai = wid; ai < n; ai += nw) {
+  {
+    const u32 i = threadIdx.x;
+    s_hash[0][i] = (u64)((i & 3u) + 1u) + (u64)(((i >> 2) & 3u) + 1u) * P1 +
+                   (u64)(((i >> 4) & 3u) + 1u) * P2 + (u64)((i >> 6) + 1u) * P3;
+    s_hash[1][i] = s_hash[0][i] * P1 * P3;
+    if (i < 10) {
+      u32 v = 1;
+      for (u32 e = 0; e < i; ++e) v *= 10u;
+      s_pow10[i] = v;
+    }
+  }
+  __syncthreads();
+  const u64 n = pair_n(namp, acap);
+  // each XCD (workgroups are placed on them round robin) its own run of amplicons
+  const u32 nx = (gridDim.x & 7u) == 0u ? 8u : 1u, x = blockIdx.x % nx;
+  const u64 end_x = n * (x + 1) / nx, stride = (u64)(gridDim.x / nx) * (kBlock / 64);
+  const u64 p_lane = pow_p(8u * lane), Q = pow_p(kFastaStep);
+  // the wave's number is uniform: an amplicon's fields live in scalar registers
+  const u32 wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  for (u64 ai = n * x / nx + (u64)(blockIdx.x / nx) * (kBlock / 64) + wv; ai < end_x; ai += stride) {
     const ah_amplicon A = amp[ai];
     if (A.genome >= n_genomes) continue;  // not written by a pairing of these genomes
     const u64 at = rec_at[ai];
@@ -2050,57 +2228,20 @@ __global__ __launch_bounds__(kBlock) void k_fasta_write(
     const u32 rl = rec_len[ai];
     const u32 hl = rl - len - 1u;
     const bool fits = at + rl <= tcap;
-    if (fits && lane == 0) {
-      char* o = text + at;
-      o = put_str(o, ">g");
-      o = put_dec(o, A.genome);
-      *o++ = ':';
-      o = put_dec(o, A.start);
-      *o++ = '-';
-      o = put_dec(o, A.end);
-      o = put_str(o, " pair=");
-      o = put_dec(o, A.pair);
-      o = put_str(o, A.orient == AH_FR ? " orient=FR" : A.orient == AH_RF ? " orient=RF"
-                     : A.orient == AH_FF ? " orient=FF" : " orient=RR");
-      o = put_str(o, " tm=");
-      o = put_tm(o, hits[A.plus_hit].tm);
-      *o++ = ',';
-      o = put_tm(o, hits[A.minus_hit].tm);
-      *o++ = '\n';
-      text[at + rl - 1u] = '\n';
+    if (fits) {
+      const float tp = hits[A.plus_hit].tm, tm = hits[A.minus_hit].tm;
+      for (u32 p = lane; p < hl; p += 64u) text[at + p] = fasta_header_char(A, tp, tm, p, s_pow10);
+      if (lane == 0) text[at + rl - 1u] = '\n';
     }
-    const int S = (int)(((u64)glen[A.genome] + 31u) >> 5);  // len up to 2^32 - 1
-    const uint2* w = words + word_off[A.genome];
-    const u32* nm = nmask ? nmask + word_off[A.genome] : nullptr;
-    const bool rc = A.orient == AH_RF;
-    // base x = b * S + t of this lane's first position; then x moves by 64
-    const int x0 = rc ? (int)A.end - 1 - (int)lane : (int)A.start + (int)lane;
-    int b = x0 / S, t = x0 - b * S;
-    char* out = text + at + hl;
-    u64 acc = 0, qp = 1;
-    for (u32 k = lane; k < len; k += 64u) {
-      const uint2 v = w[t];
-      u32 c = (((v.x >> b) & 1u) << 1) | ((v.y >> b) & 1u);
-      if (nm && ((nm[t] >> b) & 1u)) c = 4u;
-      else if (rc) c = 3u - c;
-      if (fits) out[k] = "ACGTN"[c];
-      acc += (u64)(c + 1u) * qp;
-      qp *= Q;
-      if (rc) {
-        t -= 64;
-        while (t < 0) {
-          t += S;
-          --b;
-        }
-      } else {
-        t += 64;
-        while (t >= S) {
-          t -= S;
-          ++b;
-        }
-      }
-    }
-    acc *= p_lane;
+    const FastaSeq F{words + word_off[A.genome],
+                     nmask ? nmask + word_off[A.genome] : nullptr,
+                     fits ? text + at + hl : nullptr,
+                     A.start,
+                     A.end,
+                     (u32)(((u64)glen[A.genome] + 31u) >> 5),  // len up to 2^32 - 1
+                     len,
+                     A.orient == AH_RF};
+    u64 acc = fasta_sequence(F, lane, s_hash, Q) * p_lane;
     for (u32 o = 32; o > 0; o >>= 1) acc += __shfl_xor(acc, o, 64);
     if (lane == 0) {
       const u64 h = mix64(acc ^ (u64)len);
@@ -2461,14 +2602,15 @@ hipError_t launch_fasta(const ah_genomes& g, const ah_hit* hits, const ah_amplic
                         const ah_result* namp, uint64_t acap, uint32_t n_pairs, char* text,
                         uint64_t tcap, ah_result* res, uint64_t* seq_hash, uint64_t* atype,
                         uint32_t* atype_n, uint32_t* rec_len, uint64_t* rec_at, uint64_t* cc,
-                        int waves, hipStream_t st) {
+                        int cus, hipStream_t st) {
   const u64 n_groups = (u64)n_pairs * g.n;
   k_fasta_len<<<kPairGrid, kBlock, 0, st>>>(amp, namp, acap, hits, rec_len, (u64*)cc, (u64*)atype,
                                            atype_n, n_groups);
   k_fasta_offsets<<<kPairGrid, kBlock, 0, st>>>(namp, acap, rec_len, (const u64*)cc, (u64*)rec_at,
                                                tcap, res);
-  const int blocks = (waves + kBlock / 64 - 1) / (kBlock / 64);
-  k_fasta_write<<<blocks > 0 ? blocks : 1, kBlock, 0, st>>>(
+  // what is resident at once, no more than the capacity can use
+  const u64 blocks = std::min<u64>((u64)cus * kFastaBlocks, (acap + kBlock / 64 - 1) / (kBlock / 64));
+  k_fasta_write<<<blocks > 0 ? (u32)blocks : 1u, kBlock, 0, st>>>(
       (const uint2*)g.words, g.nmask, (const u64*)g.word_off, g.len, g.n, amp, namp, acap, hits,
       rec_len, (const u64*)rec_at, text, tcap, (u64*)seq_hash, (u64*)atype, atype_n, n_pairs);
   return hipGetLastError();

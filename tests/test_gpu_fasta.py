@@ -100,3 +100,17 @@ def test_fasta_overflow_reports_the_size(dev):
     torch.cuda.synchronize()
     assert path.result(fb2.text_res)["status"] == 0
     assert len(path.fasta_text(fb2)) == len(want)
+
+
+# amplicons around the writer's 4-base and 256-base steps, in genomes whose
+# segments are shorter than a step (and than four bases)
+@pytest.mark.parametrize("len_lo,len_hi,nruns", [(24, 130, 0), (300, 1300, 40), (1000, 3000, 0)])
+def test_fasta_steps_of_the_writer(len_lo, len_hi, nruns, dev):
+    pair = plan.PairSpec("ACGTNN", "GGNTCA", k=1, clamp=0, min_len=12, max_len=1100)
+    p = plan.tiny(720 + len_lo, n_genomes=40 if len_lo < 300 else 10, len_lo=len_lo, len_hi=len_hi, pair=pair,
+                  n_copies=(0, 1), nruns=nruns, span=20)
+    _, _, _, r, want = check(p, [pair], dev, text_cap=1 << 26)
+    lens = {len(x) for x in want.split(b"\n")[1::2]}
+    say("writer steps", len_lo, "lengths", len(lens), "records", want.count(b">"))
+    assert r["status"] == 0 and {x % 4 for x in lens} == {0, 1, 2, 3}
+    assert len_lo < 300 or {255, 256, 257} & lens
