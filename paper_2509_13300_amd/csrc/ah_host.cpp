@@ -1888,28 +1888,30 @@ ah_status tm_table(const PairSet& ps, uint32_t n_pairs, const ah_tm_params& pp, 
       memset(&t, 0, sizeof t);
       t.L = (uint32_t)pr.L;
       t.k = ps.k[q];
-      uint64_t deg = 1;
+      const bool want_gc = salt_t.recip && salt_t.b < 0.0;  // G+C raises Tm
+      auto reads_gc = [&](uint8_t set) {  // C = 1, G = 2
+        const bool gc = (set & 0x6) != 0, at = (set & 0x9) != 0;
+        return want_gc ? gc : !at;
+      };
       for (int j = 0; j < pr.L; ++j) {
         const uint8_t m = pr.mask[j];
-        const int cnt = __builtin_popcount(m);
-        t.lanes |= 1ull << (2 * j);
-        if (j < pr.L - 1) t.stackm |= 1ull << (2 * j);
-        if (cnt == 1) {
+        const uint64_t bit = 1ull << (2 * j);
+        t.lanes |= bit;
+        if (j < pr.L - 1) t.stackm |= bit;
+        if (__builtin_popcount(m) == 1) {
           t.fixed |= (uint64_t)__builtin_ctz(m) << (2 * j);
-        } else {
-          uint8_t packed = 0;
-          int r = 0;
-          for (int b = 0; b < 4; ++b)
-            if (m >> b & 1) packed |= (uint8_t)(b << (2 * r++));
-          t.dpos[t.nd] = (uint8_t)j;
-          t.nmem[t.nd] = (uint8_t)cnt;
-          t.mem[t.nd] = packed;
-          t.nd++;
-          deg = deg > (~0ull >> 2) ? ~0ull : deg * (uint64_t)cnt;  // saturates
+          continue;
         }
+        t.degm |= bit;
+        t.first |= (uint64_t)__builtin_ctz(m) << (2 * j);
+        if (reads_gc(m)) t.gc_all |= bit;
+        for (int b = 0; b < 4; ++b)
+          if (m >> b & 1) {
+            t.has[b] |= bit;
+            if (reads_gc((uint8_t)(m & ~(1u << b)))) t.gc_wo[b] |= bit;
+          }
       }
       for (uint32_t j = 0; j < ps.clamp[q]; ++j) t.clampm |= 1ull << (2 * (pr.L - 1 - (int)j));
-      t.deg = deg;
       t.decoy = (ps.flags[q] & AH_PAIR_DECOY) ? 1u : 0u;
       t.KL = tm_denominator_const(*p, salt_t, pr.L);
       t.dp = tm_exact_route(pr, ps.k[q], ps.clamp[q], *p, salt_t) ? 1u : 0u;

@@ -23,20 +23,24 @@ constexpr int kScanU = 19;         // default window words per lane (odd) in the
 // bits 2j..2j+1; the masks below have bit 2j set for the positions they name.
 struct PrimerTab {
   uint64_t fixed;     // codes of the non-degenerate positions (0 at degenerate ones)
+  uint64_t first;     // codes of the first member at degenerate positions (A<C<G<T)
   uint64_t lanes;     // positions 0..L-1
   uint64_t clampm;    // clamp positions L-c..L-1 (the primer's 3' end)
   uint64_t stackm;    // positions 0..L-2 (left base of each stack)
-  uint64_t deg;       // oligos in the expansion
+  uint64_t degm;      // degenerate positions
+  uint64_t has[4];    // degenerate positions whose set holds base b
+  // Salt methods 6 and 7: degenerate positions that read as G+C when unpaired
+  // (G+C allowed if it raises Tm, else only if nothing but G+C is), with every
+  // member allowed, and without the base b that would pair
+  uint64_t gc_all, gc_wo[4];
   double KL;          // FP64: salt entropy + R ln C (+ symmetry), cal/(K mol)
   double tshift;      // salt methods 1-4: degrees added to Tm
   double rA, rB;      // salt methods 6, 7: 1/T += rA + rB * (G+C count) / L
   uint32_t recip;     // 1: apply rA, rB
-  uint32_t L, k, nd;
+  uint32_t L, k;
   uint32_t decoy;     // 1: the site is the primer against the reversed genome
   uint32_t dp;        // 1: exact best pairing (ratio iteration), not enumeration
-  uint8_t dpos[32];   // degenerate positions, 5'->3'
-  uint8_t nmem[32];   // number of members of each degenerate position
-  uint8_t mem[32];    // members, 2 bits each, in A<C<G<T order
+  uint32_t reserved;
 };
 
 // Per-pair table used by the pairing kernels.

@@ -519,21 +519,16 @@ __constant__ float c_nn_ds[16] = {
     -21.3f, -22.2f, -22.7f, -22.2f};
 constexpr float kInitGcH = 0.1f, kInitGcS = -2.8f, kInitAtH = 2.3f, kInitAtS = 4.1f;
 
-// Error-free transformation of s + x (Knuth's TwoSum); the rounding error is
-// accumulated in c.
-__device__ __forceinline__ void two_sum(float& s, float& c, float x) {
-  const float t = s + x;
-  const float bp = t - s;
-  const float err = (s - (t - bp)) + (x - bp);
-  s = t;
-  c += err;
-}
-
-__device__ __forceinline__ void init_term(u32 base, float& sh, float& ch, float& ss, float& cs) {
-  const bool gc = base == 1u || base == 2u;
-  two_sum(sh, ch, gc ? kInitGcH : kInitAtH);
-  two_sum(ss, cs, gc ? kInitGcS : kInitAtS);
-}
+// Sums of stacks are exact: as floats the Delta-H values are multiples of
+// 2^-21 and the Delta-S values of 2^-19, and 31 of them, in units of 2^-22 and
+// 2^-21, stay below 2^31.  So a sum is an int32, its value as a double (the
+// terminal pairs' floats added) has no rounding either, and Delta-H and
+// Delta-S are the correctly rounded sums of the terms, as a compensated
+// floating-point sum of them is, at one addition a term.
+typedef int2 NnFix;  // Delta-H in 2^-22, Delta-S in 2^-21
+constexpr float kFixH = 4194304.f, kFixS = 2097152.f;
+__device__ __forceinline__ double fix_h(int v) { return (double)v * 0x1p-22; }
+__device__ __forceinline__ double fix_s(int v) { return (double)v * 0x1p-21; }
 
 // The genomes and primer tables a Tm evaluation reads.
 struct TmJob {
@@ -569,13 +564,13 @@ constexpr int kDpE = AH_MAX_K + 1;
 
 // Delta-H / (Delta-S + KL) of pairing eq (bit 2j: position j paired) of
 // oligo o, in double precision; equal to N / D above.
-__device__ double pairing_ratio(u64 eq, u64 o, double KL, const float* s_dh, const float* s_ds) {
+__device__ double pairing_ratio(u64 eq, u64 o, double KL, const NnFix* s_nn) {
   double h = 0.0, s = 0.0;
   for (u64 st = eq & (eq >> 2); st; st &= st - 1) {
     const u32 j2 = (u32)__ffsll((long long)st) - 1u;
-    const u32 ix = (u32)(((o >> j2) & 3u) << 2) | (u32)((o >> (j2 + 2u)) & 3u);
-    h += (double)s_dh[ix];
-    s += (double)s_ds[ix];
+    const NnFix v = s_nn[(u32)(o >> j2) & 15u];
+    h += fix_h(v.x);
+    s += fix_s(v.y);
   }
   if (eq) {
     const u32 ends[2] = {(u32)__ffsll((long long)eq) - 1u, 63u - (u32)__clzll((long long)eq)};
@@ -593,12 +588,12 @@ __device__ double pairing_ratio(u64 eq, u64 o, double KL, const float* s_dh, con
 // afree unpaired (bit 2j: position j paired); o: the representative oligo.
 // Not inlined: the enumeration route's kernels keep their own registers.
 __device__ __noinline__ u64 tm_dp_pairing(u64 o, u64 eq0, u64 afree, u32 budget, u32 L, double KL,
-                                          const float* s_dh, const float* s_ds) {
+                                          const NnFix* s_nn) {
   const double kNeg = -__builtin_inf();
   double v[4][kDpE];
   u32 m[4][kDpE];
   u64 best = eq0;
-  double rbest = pairing_ratio(eq0, o, KL, s_dh, s_ds);
+  double rbest = pairing_ratio(eq0, o, KL, s_nn);
   budget = min(budget, (u32)(kDpE - 1));
   for (int it = 0; it < 64; ++it) {
     const double lam = rbest;
@@ -617,8 +612,8 @@ __device__ __noinline__ u64 tm_dp_pairing(u64 o, u64 eq0, u64 afree, u32 budget,
       const double wi = -(double)(gc ? kInitGcH : kInitAtH) + lam * (double)(gc ? kInitGcS : kInitAtS);
       double ws = kNeg;
       if (j > 0u && can_pair && ((eq0 >> (j2 - 2u)) & 1u) != 0u) {
-        const u32 ix = (((u32)(o >> (j2 - 2u)) & 3u) << 2) | b;
-        ws = -(double)s_dh[ix] + lam * (double)s_ds[ix];
+        const NnFix v = s_nn[(u32)(o >> (j2 - 2u)) & 15u];
+        ws = -fix_h(v.x) + lam * fix_s(v.y);
       }
       const u32 bit = 1u << j;
       // descending e: an unpaired free position reads e - 1 before it is
@@ -661,7 +656,7 @@ __device__ __noinline__ u64 tm_dp_pairing(u64 o, u64 eq0, u64 afree, u32 budget,
     }
     u64 eq = 0;
     for (u32 j = 0; j < L; ++j) eq |= (u64)((fm >> j) & 1u) << (2u * j);
-    const double r = pairing_ratio(eq, o, KL, s_dh, s_ds);
+    const double r = pairing_ratio(eq, o, KL, s_nn);
     if (!(r > rbest)) break;
     rbest = r;
     best = eq;
@@ -708,17 +703,23 @@ struct TmRep {
   u64 afree;   // in-set, non-clamp positions a pairing may unpair
   u64 st0;     // its stacks (bit 2j: positions j, j + 1 paired)
   u64 gp, gu;  // G+C bits (salt methods 6 and 7)
-  float sh0, ch0, ss0, cs0;  // its stack sums, compensated
+  int h0, s0;  // its stack sums (fixed point)
   u32 budget;  // positions of afree a pairing may unpair
   u32 nfree;   // positions in afree
   bool ok;     // some oligo of the primer is compatible with the site
 };
 
+// Positions (two bits each, from bit 0) in reverse order: L of them.
+__device__ __forceinline__ u64 reverse_positions(u64 v, u32 L) {
+  const u64 r = __builtin_bitreverse64(v);
+  return (((r & 0x5555555555555555ull) << 1) | ((r >> 1) & 0x5555555555555555ull)) >> (64u - 2u * L);
+}
+
 // Site record h (a genome and pair of this call); T: its primer's table;
-// S: the segment words of the site's genome, wbase: its first word; s_dh /
-// s_ds: the stack tables in LDS.
+// S: the segment words of the site's genome, wbase: its first word; s_nn: the
+// stack table in LDS.
 __device__ __forceinline__ TmRep tm_rep(const TmJob& J, const ah_hit& h, u64 S, u64 wbase,
-                                        const float* s_dh, const float* s_ds,
+                                        const NnFix* s_nn,
                                         const PrimerTab* T) {
   const uint2* __restrict__ words = J.words;
   const u32* __restrict__ nmask = J.nmask;
@@ -735,85 +736,91 @@ __device__ __forceinline__ TmRep tm_rep(const TmJob& J, const ah_hit& h, u64 S, 
   // the + strand of a decoy site (the decoy's + pattern is the primer's
   // complement: the primer against the reversed genome's - strand).
   const u32 cflip = strand ^ T->decoy;
-  // All 32 words a primer can span are loaded at once, unconditionally:
-  // the window word is t < S and every genome carries 31 halo words, so
-  // words t .. t + 31 lie inside its allocation (and its mask's).
+  const u64 allpos = T->lanes;
+  // The words a primer can span are loaded at once: the window word is t < S
+  // and every genome carries 31 halo words, so words t .. t + 31 lie inside
+  // its allocation (and its mask's).  The upper 16 only where a primer of the
+  // wave is that long.
+  const bool upper = __any(L > 16u);
   uint2 wv[32];
-#pragma unroll
-  for (u32 j = 0; j < 32; ++j) wv[j] = words[w0 + j];
-  u64 ow = 0;
-#pragma unroll
-  for (u32 j = 0; j < 32; ++j) {
-    const u32 c = (((wv[j].x >> b) & 1u) << 1) | ((wv[j].y >> b) & 1u);
-    const u32 jj = strand ? L - 1u - j : j;
-    if (j < L) ow |= (u64)(cflip ? 3u - c : c) << (2u * jj);
-  }
+  __builtin_memcpy(wv, words + w0, 128);
+  if (upper) __builtin_memcpy(wv + 16, words + w0 + 16, 128);
   u64 nb = 0;
   if (nmask) {
-    u32 nmv[32];
+    u32 nmv[32], n0 = 0, n1 = 0;
+    __builtin_memcpy(nmv, nmask + w0, 64);
+    if (upper) __builtin_memcpy(nmv + 16, nmask + w0 + 16, 64);
 #pragma unroll
-    for (u32 j = 0; j < 32; ++j) nmv[j] = nmask[w0 + j];
+    for (u32 j = 0; j < 16; ++j) n0 |= ((nmv[j] >> b) & 1u) << (2u * j);
+    if (upper) {
 #pragma unroll
-    for (u32 j = 0; j < 32; ++j) {
-      const u32 jj = strand ? L - 1u - j : j;
-      if (j < L) nb |= (u64)((nmv[j] >> b) & 1u) << (2u * jj);
+      for (u32 j = 0; j < 16; ++j) n1 |= ((nmv[j + 16] >> b) & 1u) << (2u * j);
     }
+    nb = (((u64)n1 << 32) | n0) & allpos;
+    if (strand) nb = reverse_positions(nb, L);
   }
-  const u64 lanes = T->lanes & ~nb;
+  u32 c0 = 0, c1 = 0;
+#pragma unroll
+  for (u32 j = 0; j < 16; ++j)
+    c0 |= ((wv[j].x >> b) & 1u) << (2u * j + 1u) | ((wv[j].y >> b) & 1u) << (2u * j);
+  if (upper) {
+#pragma unroll
+    for (u32 j = 0; j < 16; ++j)
+      c1 |= ((wv[j + 16].x >> b) & 1u) << (2u * j + 1u) | ((wv[j + 16].y >> b) & 1u) << (2u * j);
+  }
+  const u64 both = allpos * 3ull;
+  u64 ow = (((u64)c1 << 32) | c0) & both;
+  if (cflip) ow ^= both;
+  if (strand) ow = reverse_positions(ow, L);
+  const u64 lanes = allpos & ~nb;
   const u64 clampm = T->clampm;
-  const u64 stackm = T->stackm;
   const u32 k = T->k;
-  const bool recip = T->recip != 0u;
-  const bool want_gc = T->rB < 0.0;
-  u64 o = T->fixed, afree = 0, degm = 0, gu_deg = 0;
-  for (u32 d = 0; d < T->nd; ++d) {
-    const u32 pos2 = 2u * T->dpos[d];
-    const u32 t = (u32)(ow >> pos2) & 3u;
-    const u32 mem = T->mem[d];
-    bool in_set = false;
-    for (u32 q = 0; q < T->nmem[d]; ++q) in_set |= ((mem >> (2u * q)) & 3u) == t;
-    in_set &= ((nb >> pos2) & 1u) == 0u;
-    o |= (u64)(in_set ? t : (mem & 3u)) << pos2;
-    if (in_set && ((clampm >> pos2) & 1u) == 0u) afree |= 1ull << pos2;
-    if (recip) {
-      bool any_gc = false, all_gc = true;
-      for (u32 q = 0; q < T->nmem[d]; ++q) {
-        const u32 m = (mem >> (2u * q)) & 3u;
-        if (in_set && m == t) continue;
-        const bool gc = ((m ^ (m >> 1)) & 1u) != 0u;  // C = 1, G = 2
-        any_gc |= gc;
-        all_gc &= gc;
-      }
-      degm |= 1ull << pos2;
-      if (want_gc ? any_gc : all_gc) gu_deg |= 1ull << pos2;
-    }
-  }
-  const u64 allpos = T->lanes;
+  // per base, the positions whose template base it pairs with; in: degenerate
+  // positions whose set holds that base
+  const u64 hb = ow >> 1;
+  const u64 is[4] = {~(hb | ow), ~hb & ow, hb & ~ow, hb & ow};
+  u64 in = 0;
+#pragma unroll
+  for (u32 q = 0; q < 4; ++q) in |= is[q] & T->has[q];
+  in &= ~nb;
+  const u64 in2 = in * 3ull, o = T->fixed | (ow & in2) | (T->first & ~in2);
   r.o = o;
-  r.afree = afree;
+  r.afree = in & ~clampm;
   r.gp = (o ^ (o >> 1)) & allpos;
-  r.gu = (r.gp & ~degm) | gu_deg;
+  r.gu = r.gp;
+  if (T->recip != 0u) {
+    u64 gc = T->gc_all & ~in;
+#pragma unroll
+    for (u32 q = 0; q < 4; ++q) gc |= is[q] & in & T->gc_wo[q];
+    r.gu = (r.gp & ~T->degm) | gc;
+  }
   const u64 x = o ^ ow;
   r.eq0 = ~(x | (x >> 1)) & lanes;  // paired positions of the representative
   const u32 mism0 = L - (u32)__popcll(r.eq0);
   // The representative's stacks are summed once.  Another pairing turns
   // positions of it into mismatches, which only removes the stacks on
-  // either side of each: its sums are the representative's minus those
-  // (compensated sums throughout).
-  r.st0 = r.eq0 & (r.eq0 >> 2) & stackm;
-  float sh0 = 0.f, ch0 = 0.f, ss0 = 0.f, cs0 = 0.f;
-  for (u64 st = r.st0; st; st &= st - 1) {
-    const u32 j2 = (u32)__ffsll((long long)st) - 1u;
-    const u32 ix = (u32)(((o >> j2) & 3u) << 2) | (u32)((o >> (j2 + 2u)) & 3u);
-    two_sum(sh0, ch0, s_dh[ix]);
-    two_sum(ss0, cs0, s_ds[ix]);
+  // either side of each: its sums are the representative's minus those.  The
+  // positions are walked in order with zeros for absent stacks, so that the
+  // table reads wait for nothing.
+  r.st0 = r.eq0 & (r.eq0 >> 2) & T->stackm;
+  r.h0 = 0;
+  r.s0 = 0;
+#pragma unroll
+  for (u32 g = 0; g < 4; ++g) {
+    const u32 so = (u32)(r.st0 >> (16u * g)) & 0xffffu;
+    if (!__any(so != 0u)) continue;
+    const u32 oo = (u32)(o >> (16u * g));              // positions 8 g .. 8 g + 7
+    const u32 on = (u32)(o >> (16u * g + 14u)) & 15u;  // 8 g + 7 and the next
+#pragma unroll
+    for (u32 j = 0; j < 8; ++j) {
+      const NnFix v = s_nn[j < 7 ? (oo >> (2u * j)) & 15u : on];
+      const int there = -(int)((so >> (2u * j)) & 1u);
+      r.h0 += v.x & there;
+      r.s0 += v.y & there;
+    }
   }
-  r.sh0 = sh0;
-  r.ch0 = ch0;
-  r.ss0 = ss0;
-  r.cs0 = cs0;
   r.ok = mism0 <= k && (r.eq0 & clampm) == clampm;
-  r.nfree = (u32)__popcll(afree);
+  r.nfree = (u32)__popcll(r.afree);
   r.budget = r.ok ? min(k - mism0, r.nfree) : 0u;
   return r;
 }
@@ -821,22 +828,23 @@ __device__ __forceinline__ TmRep tm_rep(const TmJob& J, const ah_hit& h, u64 S, 
 // The Tm of pairing eq (a subset of r.eq0) of site r, in degrees before the
 // shift of salt methods 1-4.
 __device__ __forceinline__ float tm_pairing(const TmRep& r, const PrimerTab* T, u64 eq,
-                                            const float* s_dh, const float* s_ds) {
-  float sh = r.sh0, ch = r.ch0, ss = r.ss0, cs = r.cs0;
+                                            const NnFix* s_nn) {
+  int h = r.h0, s = r.s0;
   for (u64 st = r.st0 & ~(eq & (eq >> 2)); st; st &= st - 1) {  // the stacks eq breaks
-    const u32 j2 = (u32)__ffsll((long long)st) - 1u;
-    const u32 ix = (u32)(((r.o >> j2) & 3u) << 2) | (u32)((r.o >> (j2 + 2u)) & 3u);
-    two_sum(sh, ch, -s_dh[ix]);
-    two_sum(ss, cs, -s_ds[ix]);
+    const NnFix v = s_nn[(u32)(r.o >> ((u32)__ffsll((long long)st) - 1u)) & 15u];
+    h -= v.x;
+    s -= v.y;
   }
+  double hd = fix_h(h), sd = fix_s(s);
   if (eq) {
-    const u32 lo = (u32)__ffsll((long long)eq) - 1u;
-    const u32 hi = 63u - (u32)__clzll((long long)eq);
-    init_term((u32)(r.o >> lo) & 3u, sh, ch, ss, cs);
-    init_term((u32)(r.o >> hi) & 3u, sh, ch, ss, cs);
+    const u32 e0 = (u32)(r.o >> ((u32)__ffsll((long long)eq) - 1u)) & 3u;
+    const u32 e1 = (u32)(r.o >> (63u - (u32)__clzll((long long)eq))) & 3u;
+    const int gcs = (int)(e0 == 1u || e0 == 2u) + (int)(e1 == 1u || e1 == 2u);
+    hd += gcs == 0 ? 2.0 * kInitAtH : gcs == 1 ? (double)kInitAtH + kInitGcH : 2.0 * kInitGcH;
+    sd += gcs == 0 ? 2.0 * kInitAtS : gcs == 1 ? (double)kInitAtS + kInitGcS : 2.0 * kInitGcS;
   }
-  const float den = (float)((double)ss + (double)cs + T->KL);
-  float tm = 1000.0f * (sh + ch) / den - 273.15f;
+  const float den = (float)(sd + T->KL);
+  float tm = 1000.0f * (float)hd / den - 273.15f;
   if (T->recip) {  // 1/T += rA + rB fGC, with this pairing's best G+C count
     const u64 allpos = T->lanes;
     const u32 gc = (u32)__popcll(eq & r.gp) + (u32)__popcll(allpos & ~eq & r.gu);
@@ -846,12 +854,36 @@ __device__ __forceinline__ float tm_pairing(const TmRep& r, const PrimerTab* T, 
   return tm;
 }
 
-// C(n, r) for n <= 32.  Each partial product is a binomial below 2^30 and
-// each step's product below 2^35, so double precision carries them exactly
-// (and a correctly rounded division of an exact multiple is exact), without
-// the 64-bit integer division the device does in software.
+// Whether no other pairing of site r can be above its representative's Tm
+// (tm, no reciprocal correction).  With T that Tm in kelvin, unpairing
+// positions adds g = 1000 |Delta-H| - T |Delta-S| of every stack it breaks, and
+// of changes at the two outermost pairs, to 1000 Delta-H - T (Delta-S + KL), and
+// lowers the Tm when that sum is positive.  So it is enough that the outermost
+// pairs cannot be unpaired and that every stack next to a position that can be
+// has g > 1 (a loss above 1e-3 degrees, past every rounding).
+__device__ __forceinline__ bool tm_rep_is_best(const TmRep& r, const PrimerTab* T, float tm,
+                                               const NnFix* s_nn) {
+  if (T->recip || r.eq0 == 0) return false;
+  const u64 lo = r.eq0 & (0ull - r.eq0), hi = 1ull << (63u - (u32)__clzll((long long)r.eq0));
+  if ((r.afree & (lo | hi)) != 0ull || !(fix_s(r.s0) + T->KL < -20.0)) return false;
+  const float t = tm + 273.15f;
+  for (u64 st = r.st0 & (r.afree | (r.afree >> 2)); st; st &= st - 1) {
+    const NnFix v = s_nn[(u32)(r.o >> ((u32)__ffsll((long long)st) - 1u)) & 15u];
+    const float g = t * ((float)v.y * (1.f / kFixS)) - 1000.f * ((float)v.x * (1.f / kFixH));
+    if (!(g > 1.f)) return false;
+  }
+  return true;
+}
+
+// C(n, r) for n <= 32: in 32 bits for r <= 3, as nearly every call is.  Beyond,
+// each partial product is a binomial below 2^30 and each step's product below
+// 2^35, so double precision carries them exactly (and a correctly rounded
+// division of an exact multiple is exact), without the 64-bit integer
+// division the device does in software.
 __device__ __forceinline__ u64 binom(u32 n, u32 r) {
   if (r > n) return 0;
+  if (r <= 3u)
+    return r == 0u ? 1u : r == 1u ? n : r == 2u ? n * (n - 1u) / 2u : n * (n - 1u) * (n - 2u) / 6u;
   double c = 1.0;
   for (u32 i = 1; i <= r; ++i) c = c * (double)(n - r + i) / (double)i;
   return (u64)c;
@@ -894,7 +926,6 @@ __device__ __forceinline__ u64 shfl64(u64 v, int src) {
   const u32 lo = (u32)__shfl((int)(u32)v, src, 64), hi = (u32)__shfl((int)(u32)(v >> 32), src, 64);
   return ((u64)hi << 32) | lo;
 }
-__device__ __forceinline__ float shflf(float v, int src) { return __shfl(v, src, 64); }
 
 // A float as an int that orders like it (for LDS atomic max; NaN never
 // stored).
@@ -906,23 +937,41 @@ __device__ __forceinline__ float tm_unkey(int k) {
   return __int_as_float(k >= 0 ? k : k ^ 0x7fffffff);
 }
 
+// The next subset of mask with as many positions as sub (0 after the last):
+// Gosper's next combination, with the carry running over mask's positions only.
+__device__ __forceinline__ u64 next_subset(u64 sub, u64 mask) {
+  const u64 low = sub & (0ull - sub);
+  u64 v = ((sub | ~mask) + low) & mask;
+  if (v == 0) return 0;
+  u64 m = mask;  // the positions lost to the carry return as the lowest ones
+  for (u32 n = (u32)__popcll(sub) - (u32)__popcll(v); n; --n, m &= m - 1ull) v |= m & (0ull - m);
+  return v;
+}
+
 // The Tm of each lane's site record h (valid: the lane has one; every lane
 // of the wave calls this together).  T2: the lane's pair's two primer
 // tables; s_best: 64 ints of LDS for this wave.  The representative pairing
-// is evaluated by its own lane.  The other pairings of all the wave's sites
-// are then dealt out over the 64 lanes in turn (a site with many pairings no
-// longer holds the wave while the others idle): lane l takes pairings l,
-// l + 64, ... of the wave's list, finds the site each belongs to and its
-// subset, and its Tm goes to the site's slot by an atomic max.  A wave whose
-// sites have at most kTmLaneMax extra pairings each keeps them in their own
-// lanes (a round of the dealing costs more than a few pairings).  Primers
-// that take the exact route (kExact and the table's dp) find their best
-// pairing by tm_dp_pairing in their own lane instead.
-constexpr u64 kTmLaneMax = 4;
+// is evaluated by its own lane.  Most sites need no other (tm_rep_is_best).
+// Else the lane goes through them, each a few stacks off the representative's
+// sums; where one site of the wave has many more than the rest, the pairings of
+// all the wave's sites are dealt out over the 64 lanes instead (it would hold
+// the wave while the others idle): lane l takes pairings l, l + 64, ... of the
+// wave's list, finds the site each belongs to and its subset, and its Tm goes
+// to the site's slot by an atomic max.  A round of the dealing costs about four
+// pairings of the other way.  Primers that take the exact route (kExact and the
+// table's dp) find their best pairing by tm_dp_pairing in their own lane.
+//
+// Bound by latency and instruction issue: a wave of sites is one stream of a
+// few hundred instructions after one round of loads.  Measured inside the
+// segmented tail (one wave, 8 sites of a 19/20-nt pair at k = 2): 4.0 us from the
+// loads to the Tm; 8.3 us with compensated sums, member loops per degenerate
+// position and every pairing evaluated.  The radix tail's first pass with the
+// Tm of 290,000 sites (k = 3, magnesium salt model): 76 us, 111 us before.
+constexpr u64 kTmDeal = 4;
 template <bool kExact>
 __device__ __forceinline__ float tm_wave(const TmJob& J, const ah_hit& h, bool valid, u64 S,
-                                         u64 wbase, const float* s_dh, const float* s_ds,
-                                         const PrimerTab* T2, int* s_best) {
+                                         u64 wbase, const NnFix* s_nn, const PrimerTab* T2,
+                                         int* s_best) {
   const int lane = (int)(threadIdx.x & 63u);
   const PrimerTab* T = &T2[h.strand_primer & 1u];
   TmRep r{};
@@ -930,52 +979,42 @@ __device__ __forceinline__ float tm_wave(const TmJob& J, const ah_hit& h, bool v
   u64 own = 0;                                // this site's extra pairings
   constexpr int kNoTm = (int)0x80000000;      // below every tm_key
   if (valid) {
-    r = tm_rep(J, h, S, wbase, s_dh, s_ds, T);
+    r = tm_rep(J, h, S, wbase, s_nn, T);
     if (r.ok) {
-      best = tm_pairing(r, T, r.eq0, s_dh, s_ds);
+      best = tm_pairing(r, T, r.eq0, s_nn);
       if (kExact && T->dp != 0u) {
         if (r.budget) {  // too many pairings to enumerate: the exact route
           const float v = tm_pairing(
-              r, T, tm_dp_pairing(r.o, r.eq0, r.afree, r.budget, T->L, T->KL, s_dh, s_ds), s_dh,
-              s_ds);
+              r, T, tm_dp_pairing(r.o, r.eq0, r.afree, r.budget, T->L, T->KL, s_nn), s_nn);
           best = best >= v ? best : v;
         }
-      } else {
+      } else if (r.budget && !tm_rep_is_best(r, T, best, s_nn)) {
         own = extra_pairings(r.nfree, r.budget);
       }
     }
   }
-  u64 most = own;
+  if (!__any(own != 0ull)) return valid ? best + (float)T->tshift : best;
+  // own <= AH_TM_MAX_PAIRINGS: 32 bits hold the wave's sum
+  u32 most = (u32)own;
 #pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    const u64 y = ((u64)(u32)__shfl_xor((int)(u32)(most >> 32), o, 64) << 32) |
-                  (u32)__shfl_xor((int)(u32)most, o, 64);
-    most = y > most ? y : most;
-  }
-  if (most <= kTmLaneMax) {
-    // every e-subset of the free positions, e <= budget (Gosper's next
-    // combination over nfree bits, deposited onto the position mask)
-    for (u32 e = 1; own && e <= r.budget; ++e) {
-      u64 comb = (1ull << e) - 1ull;
-      while (comb < (1ull << r.nfree)) {  // nfree <= 32
-        u64 sub = 0, m = r.afree, c = comb;
-        while (c) {
-          if (c & 1ull) sub |= m & (0ull - m);
-          m &= m - 1ull;
-          c >>= 1;
-        }
-        const float v = tm_pairing(r, T, r.eq0 & ~sub, s_dh, s_ds);
-        best = (best == best && best >= v) ? best : v;
-        const u64 low = comb & (0ull - comb);
-        const u64 nx = comb + low;
-        if (nx == 0) break;
-        comb = (((nx ^ comb) >> 2) >> (__ffsll((long long)low) - 1)) | nx;  // low: a power of two
+  for (int o = 32; o > 0; o >>= 1) most = max(most, (u32)__shfl_xor((int)most, o, 64));
+  const u64 incl = wave_incl_scan(own);
+  const u64 total = shfl64(incl, 63);
+  if (most <= kTmDeal * ((total + 63) / 64)) {
+    // every e-subset of the free positions, e <= budget
+    u64 sub = r.afree & (0ull - r.afree);
+    for (u32 e = 1; own;) {
+      const float v = tm_pairing(r, T, r.eq0 & ~sub, s_nn);
+      best = (best == best && best >= v) ? best : v;
+      sub = next_subset(sub, r.afree);
+      if (sub == 0) {
+        if (++e > r.budget) break;
+        u64 m = r.afree;  // the e lowest positions
+        for (u32 n = e; n; --n, m &= m - 1ull) sub |= m & (0ull - m);
       }
     }
     return valid ? best + (float)T->tshift : best;  // salt methods 1-4 (NaN stays NaN)
   }
-  const u64 incl = wave_incl_scan(own);
-  const u64 total = shfl64(incl, 63);
   {
     s_best[lane] = kNoTm;
     for (u64 g0 = 0; g0 < total; g0 += 64) {
@@ -994,17 +1033,15 @@ __device__ __forceinline__ float tm_wave(const TmJob& J, const ah_hit& h, bool v
       q.st0 = shfl64(r.st0, site);
       q.gp = shfl64(r.gp, site);
       q.gu = shfl64(r.gu, site);
-      q.sh0 = shflf(r.sh0, site);
-      q.ch0 = shflf(r.ch0, site);
-      q.ss0 = shflf(r.ss0, site);
-      q.cs0 = shflf(r.cs0, site);
+      q.h0 = __shfl(r.h0, site, 64);
+      q.s0 = __shfl(r.s0, site, 64);
       q.nfree = (u32)__shfl((int)r.nfree, site, 64);
       q.budget = (u32)__shfl((int)r.budget, site, 64);
       const PrimerTab* Tq = (const PrimerTab*)shfl64((u64)(uintptr_t)T, site);
       const u64 first = shfl64(incl - own, site);
       if (g < total) {
         const u64 sub = unrank_pairing(g - first, q.afree, q.nfree, q.budget);
-        const float v = tm_pairing(q, Tq, q.eq0 & ~sub, s_dh, s_ds);
+        const float v = tm_pairing(q, Tq, q.eq0 & ~sub, s_nn);
         if (v == v) atomicMax(&s_best[site], tm_key(v));
       }
     }
@@ -1027,8 +1064,7 @@ __device__ __forceinline__ bool tm_record_ok(const TmJob& J, const ah_hit& h) {
 // at once (i0: the wave's first index, the same in every lane).
 template <bool kExact>
 __device__ __forceinline__ void tm_records(const TmJob& J, ah_hit* __restrict__ hits, u64 i0,
-                                           u64 n, const float* s_dh, const float* s_ds,
-                                           int* s_best) {
+                                           u64 n, const NnFix* s_nn, int* s_best) {
   const u64 i = i0 + (threadIdx.x & 63u);
   ah_hit h{};
   bool valid = false;
@@ -1038,7 +1074,7 @@ __device__ __forceinline__ void tm_records(const TmJob& J, ah_hit* __restrict__ 
   }
   const u32 g = valid ? h.genome : 0u, pair = valid ? (u32)h.pair : 0u;
   const u64 S = valid ? ((u64)J.len[g] + 31) >> 5 : 1u, wbase = valid ? J.word_off[g] : 0u;
-  const float v = tm_wave<kExact>(J, h, valid, S, wbase, s_dh, s_ds, &J.tabs[pair * 2u], s_best);
+  const float v = tm_wave<kExact>(J, h, valid, S, wbase, s_nn, &J.tabs[pair * 2u], s_best);
   if (valid) {
     h.tm = v;
     hits[i] = h;
@@ -1046,11 +1082,9 @@ __device__ __forceinline__ void tm_records(const TmJob& J, ah_hit* __restrict__ 
 }
 
 // Loads the stack tables into LDS (every thread of the block calls this).
-__device__ __forceinline__ void tm_tables(float* s_dh, float* s_ds) {
-  if (threadIdx.x < 16) {
-    s_dh[threadIdx.x] = c_nn_dh[threadIdx.x];
-    s_ds[threadIdx.x] = c_nn_ds[threadIdx.x];
-  }
+__device__ __forceinline__ void tm_tables(NnFix* s_nn) {
+  const u32 i = threadIdx.x, ix = (i & 3u) * 4u + ((i >> 2) & 3u);  // 5' base in the low bits
+  if (i < 16) s_nn[i] = make_int2((int)(c_nn_dh[ix] * kFixH), (int)(c_nn_ds[ix] * kFixS));
   __syncthreads();
 }
 
@@ -1058,14 +1092,14 @@ template <bool kExact>
 __global__ __launch_bounds__(kBlock) void k_tm(TmJob J, ah_hit* __restrict__ hits,
                                                const ah_result* __restrict__ nhits, u64 cap) {
   // the stack tables in LDS: lanes index them divergently, once per stack
-  __shared__ float s_dh[16], s_ds[16];
+  __shared__ NnFix s_nn[16];
   __shared__ int s_best[kBlock];  // per wave: the best pairing of each lane's site
-  tm_tables(s_dh, s_ds);
+  tm_tables(s_nn);
   const u64 cnt = nhits->count;
   const u64 n = cnt < cap ? cnt : cap;
   // a wave takes 64 consecutive records at a time (the stride is whole waves)
   for (u64 i0 = global_tid() - (threadIdx.x & 63u); i0 < n; i0 += grid_threads())
-    tm_records<kExact>(J, hits, i0, n, s_dh, s_ds, s_best + (threadIdx.x & ~63u));
+    tm_records<kExact>(J, hits, i0, n, s_nn, s_best + (threadIdx.x & ~63u));
 }
 
 // ----------------------------------------------------------- pairing ----
@@ -1674,7 +1708,7 @@ __global__ __launch_bounds__(kSegBlock) void k_seg_tail(SegArgs A) {
   __shared__ u32 spos[kSegLds];
   __shared__ unsigned short pcf[kSegLds], pcr[kSegLds];
   __shared__ unsigned char kind[kSegLds];
-  __shared__ float s_dh[16], s_ds[16];
+  __shared__ NnFix s_nn[16];
   __shared__ PrimerTab s_tab[2];  // the pair's primer tables, read throughout the Tm
   __shared__ int s_best[kSegBlock];  // the best pairing of each lane's site
   const u32 t = threadIdx.x, s = blockIdx.x;
@@ -1689,7 +1723,7 @@ __global__ __launch_bounds__(kSegBlock) void k_seg_tail(SegArgs A) {
   static_assert(sizeof(PrimerTab) % 4 == 0, "primer tables copy as words");
   for (u32 i = t; i < 2 * sizeof(PrimerTab) / 4; i += kSegBlock)
     ((u32*)s_tab)[i] = ((const u32*)(A.tj.tabs + 2 * pair))[i];
-  tm_tables(s_dh, s_ds);  // its barrier also covers the copy
+  tm_tables(s_nn);  // its barrier also covers the copy
   const bool sites_ok = status == AH_OK;
   if (!sites_ok) {  // the sites overflowed: the pairing needs all of them
     if (s == 0 && t == 0) {
@@ -1733,7 +1767,7 @@ __global__ __launch_bounds__(kSegBlock) void k_seg_tail(SegArgs A) {
     for (int q = 0; q < 4; ++q) hv[q] = __shfl(hv[q], from, 64);
     ah_hit r;
     __builtin_memcpy(&r, hv, sizeof r);
-    const float tmv = tm_wave<kExact>(A.tj, r, t < m, S, wbase, s_dh, s_ds, s_tab, s_best);
+    const float tmv = tm_wave<kExact>(A.tj, r, t < m, S, wbase, s_nn, s_tab, s_best);
     if (t < m) {
       r.tm = tmv;
       o[t] = r;
@@ -1817,7 +1851,7 @@ __global__ __launch_bounds__(kSegBlock) void k_seg_tail(SegArgs A) {
       const u32 i = r0 + t;
       ah_hit h{};
       if (i < m) h = small ? A.staged[base + (u32)(keys[i] & (kSegLds - 1u))] : o[i];
-      const float tmv = tm_wave<kExact>(A.tj, h, i < m, S, wbase, s_dh, s_ds, s_tab, s_best);
+      const float tmv = tm_wave<kExact>(A.tj, h, i < m, S, wbase, s_nn, s_tab, s_best);
       if (i < m) {
         h.tm = tmv;
         o[i] = h;
@@ -2326,9 +2360,9 @@ __global__ __launch_bounds__(kBlock) void k_sort_scatter_tm(
                     nullptr, NoWritten{});
     return;
   }
-  __shared__ float s_dh[16], s_ds[16];
+  __shared__ NnFix s_nn[16];
   __shared__ int s_best[kBlock];  // per wave: the best pairing of each lane's site
-  tm_tables(s_dh, s_ds);
+  tm_tables(s_nn);
   const u64 n = *n_dev;
   const u64 t = (u64)(blockIdx.x - kSortGrid) * kBlock + threadIdx.x;
   const u64 stride = (u64)(gridDim.x - kSortGrid) * kBlock;
@@ -2337,7 +2371,7 @@ __global__ __launch_bounds__(kBlock) void k_sort_scatter_tm(
     cr[c] = 0;
   }
   for (u64 i0 = t - (threadIdx.x & 63u); i0 < n; i0 += stride)
-    tm_records<kExact>(J, staged, i0, n, s_dh, s_ds, s_best + (threadIdx.x & ~63u));
+    tm_records<kExact>(J, staged, i0, n, s_nn, s_best + (threadIdx.x & ~63u));
 }
 
 // Last pass: as a record reaches its place, the kept minus sites of the fwd
