@@ -917,8 +917,9 @@ std::string gen_program_uncached(const std::vector<Pattern>& pats, bool has_n, T
         uniform &= pats[r].pair == pats[q].pair;
   snprintf(buf, sizeof buf,
            "#define AH_U %d\n#define AH_HALO %d\n#define AH_HAS_N %d\n#define AH_WAVE %d\n"
-           "#define AH_QUAD_ONE_PAIR %d\n#define AH_TILE_COUNT %d\n",
-           tn.u, lmax - 1, has_n ? 1 : 0, wave ? 1 : 0, uniform ? 1 : 0, tile_count ? 1 : 0);
+           "#define AH_QUAD_ONE_PAIR %d\n#define AH_TILE_COUNT %d\n#define AH_PAIRS %uu\n",
+           tn.u, lmax - 1, has_n ? 1 : 0, wave ? 1 : 0, uniform ? 1 : 0, tile_count ? 1 : 0,
+           pats.empty() ? 1u : pats.back().pair + 1u);
   std::string head = buf;
   for (size_t i = 0; i < pats.size(); ++i) {
     s += gen_filter(i, pats[i], plan_filter(pats[i], allow));
@@ -1513,28 +1514,45 @@ ah_status check_genomes(const ah_genomes* g) {
 
 // Segment buffers of ah_query, carved from the workspace's radix-sort
 // buffers, which its segmented tail does not use.  False when the segments
-// are more than kSegMax or do not fit there.
-bool carve_seg(const ScanWs& w, uint32_t n_genomes, uint64_t n_seg, ah::SegBuffers& sg) {
+// are more than kSegMax, their sort keys too wide, or the buffers do not fit.
+bool carve_seg(const ScanWs& w, uint32_t n_genomes, uint64_t n_seg, uint64_t cap,
+               const ah::KeyBits& kb, ah::SegBuffers& sg) {
   if (n_seg == 0 || n_seg > ah::kSegMax) return false;
+  // a tile's keys: its segments, pos << 2 | strand-primer, 12 bits of index
+  if (bits_for(n_seg - 1) + kb.pb + 2 + 12 > 63) return false;
   const uintptr_t beg = (uintptr_t)w.sb.keys[0];
   const uintptr_t end = (uintptr_t)w.sb.hist[2] +
                         (uintptr_t)ah::kSortDigits * w.sb.hstride * sizeof(uint32_t);
   Carver c((void*)beg, (size_t)(end - beg));
-  sg.cnt = c.take<uint32_t>(4 * n_seg);  // counts, fill counters, look-back words
+  // Small capacities: workgroups of one wave, whose tiles of a few dozen sites
+  // pass through with no barrier (16 references 34.2 us a query against 36.1,
+  // 20,000 contigs with 18,000 sites 144 against 156 us).  Beyond 2^17 sites, tiles of
+  // hundreds (430,000 sites of a 64-pair panel 8.45 ms against 8.57).
+  sg.wide = cap > 131072;
+  sg.t_n = sg.wide ? 512 : 128;
+  sg.t_seg = sg.wide ? 1024 : 128;
+  sg.n_tiles = (uint32_t)std::min<uint64_t>(std::max<uint64_t>(1024, (cap + sg.t_n - 1) / sg.t_n),
+                                            cap / 32 + 1);
+  sg.n_zero = (uint32_t)(2 * n_seg + 2 * (uint64_t)sg.n_tiles);
+  sg.cnt = c.take<uint32_t>(sg.n_zero);  // counts, fill counters, look-back words
   sg.fill = sg.cnt + n_seg;
   sg.lb = (uint64_t*)(sg.cnt + 2 * n_seg);
   sg.off = c.take<uint64_t>(n_seg + 1);
+  sg.tile_base = c.take<uint64_t>(sg.n_tiles + 1);
+  sg.tile_seg = c.take<uint32_t>(sg.n_tiles + 1);
+  sg.tile_meta = c.take<uint64_t>(2);
   sg.n_seg = (uint32_t)n_seg;
   sg.n_genomes = n_genomes;
   return c.cur <= c.end;
 }
 
-// The segmented tail gives each (pair, genome) segment one wave, which takes
-// the segment's sites 64 at a time: past a few hundred sites per segment the
-// radix tail, which spreads every site over the whole device, is faster.  The
-// expected random sites of a pair's segment on the longest genome (both
-// primers, both strands) decide, against kSegExpected; AH_QUERY_SEGMENTED=1
-// or 0 forces one tail (the segmented one still only up to kSegMax segments).
+// The segmented tail sorts and pairs a segment in one workgroup, and the count
+// adds a segment's sites up in one place: past a few hundred sites per segment
+// the radix tail, which spreads every site over the whole device, is faster
+// (800 sites a segment on 500 genomes: 0.65 against 1.10 ms).  The expected
+// random sites of a pair's segment on the longest genome (both primers, both
+// strands) decide, against kSegExpected; AH_QUERY_SEGMENTED=1 or 0 forces one
+// tail (the segmented one still only up to kSegMax segments).
 constexpr double kSegExpected = 512.0;
 bool seg_mode(const ah_primer_pair* pairs, uint32_t n_pairs, uint32_t max_len) {
   const char* e = getenv("AH_QUERY_SEGMENTED");
@@ -1582,10 +1600,10 @@ ah_status launch_scan_kernel(const ScanFns& fn, Tuning tn, const ah_genomes* g, 
   const uint32_t group_words = (grid + 63) / 64 * 32;
   if (g->n <= ah::kSmallPrefix) {  // one launch, result reset and clearing included
     AH_HIP(ah::launch_tile_prefix_small(g->len, g->n, tile, w.tile_prefix, d_res, st,
-                                        seg ? seg->cnt : nullptr, seg ? 4 * seg->n_seg : 0,
+                                        seg ? seg->cnt : nullptr, seg ? seg->n_zero : 0,
                                         w.group_sites, group_words));
   } else {
-    if (seg) AH_HIP(ah::launch_zero_u64((uint64_t*)seg->cnt, 2 * seg->n_seg, st));
+    if (seg) AH_HIP(ah::launch_zero_u64((uint64_t*)seg->cnt, seg->n_zero / 2, st));
     AH_HIP(ah::launch_zero_u64(w.group_sites, group_words, st));
     AH_HIP(ah::launch_result_init(d_res, st));
     AH_HIP(ah::launch_tile_counts(g->len, g->n, tile, w.counts, st));
@@ -1642,6 +1660,7 @@ ah_status launch_scan_kernel(const ScanFns& fn, Tuning tn, const ah_genomes* g, 
     if (!fn.wave && !fn.tile_count)  // otherwise the filter counted its own candidates
       AH_HIP(hipModuleLaunchKernel(fn.verify, grid, 1, 1, ah::kBlock, 1, 1, 0, st, vargs, nullptr));
     if (seg) {
+      if (seg->n_seg > ah::kSegEmitMax) AH_HIP(ah::launch_seg_prefix(*seg, st));
       const uint32_t* cslice_tot = w.slice_tot;
       const uint64_t* cslice_win = w.slice_win;
       const uint32_t* ccand_sites = w.cand_sites;
@@ -1652,10 +1671,13 @@ ah_status launch_scan_kernel(const ScanFns& fn, Tuning tn, const ah_genomes* g, 
       ah_hit* out = w.staging;
       uint64_t cap = capacity;
       uint64_t* cstat = w.cstat;
+      uint64_t *tile_base = seg->tile_base, *tile_meta = seg->tile_meta;
+      uint32_t *tile_seg = seg->tile_seg, t_n = seg->t_n, t_seg = seg->t_seg;
       void* sargs[] = {&words,      &nmask,       &word_off, &len,      &ccands,
                        &slice,      &cslice_cnt,  &cslice_tot, &cslice_win, &ccand_sites,
                        &cseg_cnt,   &n_seg,       &seg_n,    &seg_off,  &seg_fill,
-                       &out,        &cap,         &d_res,    &cstat};
+                       &out,        &cap,         &d_res,    &cstat,    &tile_base,
+                       &tile_seg,   &tile_meta,   &t_n,      &t_seg};
       AH_HIP(hipModuleLaunchKernel(fn.emit_seg, grid, 1, 1, ah::kBlock, 1, 1, 0, st, sargs,
                                    nullptr));
       return AH_OK;
@@ -2291,7 +2313,7 @@ ah_status ah_query(const ah_genomes* g, const ah_primer_pair* pairs, const ah_wi
   const auto* ptab = (const ah::PairTab*)pair_tabs;
   ah::SegBuffers sg{};
   if (g->n > 0 && seg_mode(pairs, n_pairs, g->max_len) &&
-      carve_seg(w, g->n, (uint64_t)n_pairs * g->n, sg)) {
+      carve_seg(w, g->n, (uint64_t)n_pairs * g->n, hit_capacity, kb, sg)) {
     // each segment (pair, genome) sorted, its Tm and amplicons, by one workgroup
     s = launch_scan_kernel(fn, tn, g, w, d_hit_res, hit_capacity, st, nullptr, &sg);
     if (s) return s;

@@ -135,24 +135,34 @@ hipError_t launch_sort_tm_mark(ah_hit* staged, ah_hit* out, const uint64_t* n_de
 // The tail of ah_query over at most kSegMax segments (pair, genome), after
 // the scan's segmented emit has put each segment's sites at
 // off[s] .. off[s + 1] of the staging area in no particular order: one
-// launch, a workgroup of one wave per segment, sorts the segment into
-// canonical order (in LDS up to kSegLds sites), computes the Tm of every
-// site, counts the amplicons each leader + site starts, takes the amplicons
-// of the earlier segments by a look-back over lb, and writes its own.
+// launch, a workgroup per tile (the segments whose first site is one of `tile`
+// consecutive sites), puts the tile into canonical order (in LDS up to 4,096
+// sites, 1,024 for the one-wave form), computes the Tm of every site, counts
+// the amplicons each leader + site starts, takes the amplicons of the earlier
+// tiles by a look-back over lb, and writes its own.
 // key_bits: bits of pos << 2 | strand-primer; hcap: the capacity of out.
 // When the sites overflowed, the amplicon result is an overflow with count
 // and required 0 and no amplicon is written; the sites found still go to
 // out in canonical order with their Tm when they fit in hcap (a full
 // candidate list), as the separate calls write them.
-constexpr uint32_t kSegMax = 4096;  // AH_SEG_MAX of the scan core
-constexpr uint32_t kSegLds = 1024;
+constexpr uint32_t kSegMax = 1u << 17;
+constexpr uint32_t kSegEmitMax = 4096;  // AH_SEG_MAX of the scan core: beyond, seg_prefix
 struct SegBuffers {
   uint32_t* cnt;   // [n_seg] sites per segment, then
   uint32_t* fill;  // [n_seg] places taken so far, then
-  uint64_t* lb;    // [n_seg] look-back words (the three cleared together before the filter)
+  uint64_t* lb;    // [n_tiles] look-back words (the three cleared together before the filter)
   uint64_t* off;   // [n_seg + 1] first site of each segment
   uint32_t n_seg, n_genomes;
+  uint64_t* tile_base;  // [n_tiles + 1] first site of each tile
+  uint32_t* tile_seg;   // [n_tiles + 1] first segment of each tile
+  uint64_t* tile_meta;  // [2] tiles, sites
+  uint32_t t_n, t_seg;  // bounds of the sites per tile (from the count, from the mean segment)
+  uint32_t n_tiles;     // tiles at most, whatever the count
+  uint32_t n_zero;         // uint32 words to clear, from cnt on
+  bool wide;               // workgroups of 256 threads (else of one wave)
 };
+// off from cnt, when n_seg > kSegEmitMax (up to it, the emit pass does it).
+hipError_t launch_seg_prefix(const SegBuffers& sg, hipStream_t st);
 hipError_t launch_seg_tail(ah_hit* staged, ah_hit* out, uint64_t hcap, const SegBuffers& sg,
                            const ah_result* hres, int key_bits, const ah_genomes& g,
                            const PrimerTab* tm_tabs, uint32_t n_pairs, const PairTab* pair_tabs,
@@ -186,7 +196,7 @@ hipError_t launch_zero_u64(uint64_t* p, uint32_t n, hipStream_t st);
 // Tile counts of n <= kSmallPrefix genomes, their exclusive prefix
 // (prefix[n] = total), the reset of `res` and the clearing of
 // zero[0 .. n_zero) and zero64[0 .. n_zero64) (each when set), in one launch.
-constexpr uint32_t kSmallPrefix = 4096;
+constexpr uint32_t kSmallPrefix = 65536;
 hipError_t launch_tile_prefix_small(const uint32_t* len, uint32_t n, uint32_t tile_words,
                                     uint64_t* prefix, ah_result* res, hipStream_t st,
                                     uint32_t* zero = nullptr, uint32_t n_zero = 0,

@@ -236,53 +236,80 @@ __global__ void k_tile_counts(const u32* __restrict__ len, u32 n, u32 tile_words
   }
 }
 
-// Small collections (n <= kSmallPrefix): tile counts and their exclusive
-// prefix (n + 1 entries) in one workgroup of 1024 threads, and the result
-// reset, in one launch.
+// Exclusive prefix of val(0 .. n - 1) by a grid of workgroups of 1024 threads
+// that do not wait for one another: each owns kRun values and sums all the
+// values before them itself (n is at most a few thousand runs' worth of loads
+// that hit the caches, and all in flight at once), then calls put(i, prefix of
+// i) for its own.  Returns the prefix up to the end of its run (the total in the
+// last one).
 constexpr int kSmallBlock = 1024;
+constexpr u32 kRun = 4 * kSmallBlock;
 
+template <class ValF, class PutF>
+__device__ __forceinline__ u64 run_prefix(u32 n, const ValF& val, const PutF& put) {
+  __shared__ u64 wsum[2][kSmallBlock / 64];
+  const u32 t = threadIdx.x, lane = t & 63u, w = t >> 6;
+  const u32 r0 = blockIdx.x * kRun;
+  u64 before = 0;
+#pragma unroll 8
+  for (u32 i = t; i < r0; i += kSmallBlock) before += val(i);  // r0 <= n
+  u32 v[4];
+  u64 own = 0;
+#pragma unroll
+  for (u32 q = 0; q < 4; ++q) {
+    const u32 i = r0 + 4 * t + q;
+    v[q] = i < n ? val(i) : 0u;
+    own += v[q];
+  }
+  u64 x = own;
+#pragma unroll
+  for (u32 o = 1; o < 64; o <<= 1) {
+    const u64 y = __shfl_up(x, o, 64);
+    if (lane >= o) x += y;
+  }
+#pragma unroll
+  for (u32 o = 32; o > 0; o >>= 1) before += __shfl_xor(before, o, 64);
+  if (lane == 63) {
+    wsum[0][w] = x;
+    wsum[1][w] = before;
+  }
+  __syncthreads();
+  u64 run = x - own, all = 0;
+  for (u32 q = 0; q < kSmallBlock / 64; ++q) {
+    run += wsum[1][q] + (q < w ? wsum[0][q] : 0u);
+    all += wsum[1][q] + wsum[0][q];
+  }
+#pragma unroll
+  for (u32 q = 0; q < 4; ++q) {
+    const u32 i = r0 + 4 * t + q;
+    if (i < n) put(i, run);
+    run += v[q];
+  }
+  return all;
+}
+
+// Tile counts of n <= kSmallPrefix genomes and their exclusive prefix (n + 1
+// entries), the result reset, and the clearing of `zero` and `zero64` (every
+// workgroup a part).  20,000 genomes: 11 us (29 us by one workgroup, 20 values a
+// thread; six launches and 20 us as a scan in three with the clearing apart).
 __global__ __launch_bounds__(kSmallBlock) void k_tile_prefix_small(const u32* __restrict__ len, u32 n,
                                                                    u32 tile_words,
                                                                    u64* __restrict__ prefix,
                                                                    ah_result* r, u32* __restrict__ zero,
                                                                    u32 n_zero, u64* __restrict__ zero64,
                                                                    u32 n_zero64) {
-  __shared__ u64 wsum[kSmallBlock / 64];
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  for (u32 i = threadIdx.x; i < n_zero; i += kSmallBlock) zero[i] = 0u;
-  for (u32 i = threadIdx.x; i < n_zero64; i += kSmallBlock) zero64[i] = 0ull;
-  if (threadIdx.x == 0) {
+  for (u32 i = (u32)global_tid(); i < n_zero; i += (u32)grid_threads()) zero[i] = 0u;
+  for (u32 i = (u32)global_tid(); i < n_zero64; i += (u32)grid_threads()) zero64[i] = 0ull;
+  const u64 upto = run_prefix(
+      n, [&](u32 g) { return (u32)((((u64)len[g] + 31) / 32 + tile_words - 1) / tile_words); },
+      [&](u32 g, u64 at) { prefix[g] = at; });
+  if (threadIdx.x == 0 && blockIdx.x + 1 == gridDim.x) {
+    prefix[n] = upto;
     r->count = 0;
     r->required = 0;
     r->status = AH_OK;
     r->reserved = 0;
   }
-  u64 run = 0;
-  for (u32 base = 0; base < n; base += kSmallBlock) {
-    const u32 i = base + threadIdx.x;
-    u64 v = 0;
-    if (i < n) {
-      const u64 S = ((u64)len[i] + 31) >> 5;
-      v = (S + tile_words - 1) / tile_words;
-    }
-    u64 x = v;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-      const u64 y = __shfl_up(x, o, 64);
-      if (lane >= o) x += y;
-    }
-    if (lane == 63) wsum[w] = x;
-    __syncthreads();
-    u64 before = 0, total = 0;
-    for (int q = 0; q < kSmallBlock / 64; ++q) {
-      before += q < w ? wsum[q] : 0u;
-      total += wsum[q];
-    }
-    if (i < n) prefix[i] = run + before + x - v;
-    run += total;
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) prefix[n] = run;
 }
 
 // ------------------------------------------------------- prefix scans ----
@@ -1454,34 +1481,39 @@ __global__ __launch_bounds__(kBlock) void k_pair_write(
 }
 
 // ------------------------------------------------ segmented query tail ----
-// ah_query over at most kSegMax segments (pair, genome).  The scan's
-// segmented emit has put each segment's records together, in no particular
-// order, at seg_off[s] .. seg_off[s + 1] of the staging area.  k_seg_tail, one
-// one-wave workgroup per segment, puts the segment in canonical order (its
-// keys pos << 2 | strand-primer are distinct), computes every site's Tm,
-// counts the amplicons each leader + site starts (the leader, its minus
-// ranges and the count as the pairing kernels above define them, inside one
-// segment), takes the amplicons of the earlier segments by a decoupled
-// look-back over the segments' published counts, and writes its amplicons
-// there.  A segment of at most kSegLds records is sorted and searched in LDS
-// (at most 64 in registers); a longer one by its workgroup alone in global
-// memory: stable LSD radix passes between the staging area and the output,
-// an odd number of them so that the last lands in the output.
+// The tail of ah_query.  The scan's segmented emit has put the records of each
+// segment (pair, genome) together, in no particular order, at seg_off[s] ..
+// seg_off[s + 1] of the staging area.  k_query_tail takes them in tiles: tile b
+// is every segment whose first record is one of records [b T, (b + 1) T), so a
+// workgroup has a run of whole segments, many short ones or one long one (T and
+// the tiles' first segments come from the emit pass, which knows the count).  It
+// puts the tile in canonical order (the segment, then pos << 2 | strand-primer,
+// distinct inside one), computes every site's Tm, counts the amplicons each
+// leader + site starts (the leader, its minus ranges and the count as the
+// pairing kernels above define them, inside one segment), takes the amplicons
+// of the earlier tiles by a decoupled look-back over the tiles' published
+// counts, and writes its amplicons there.  A tile of at most kCap records is
+// sorted and searched in LDS, a longer one (a segment of thousands of sites) by
+// its workgroup in global memory: stable LSD radix passes between the staging
+// area and the output, an odd number of them so that the last lands in the
+// output.
 struct SegArgs {
-  ah_hit* staged;          // the segments' records (the long path sorts through it)
+  ah_hit* staged;          // the segments' records
   ah_hit* out;             // the records in canonical order
-  const u32* seg_cnt;      // records of each segment
-  const u64* seg_off;      // first record of each segment
+  const u64* seg_off;      // first record of each segment, n_seg + 1 entries
   u32 n_seg, n_genomes;    // segment s = pair * n_genomes + genome
-  const ah_result* hres;   // the sites' result: nothing is done on an overflow
+  const u64* tile_base;    // first record of each tile, then the records' number
+  const u32* tile_seg;     // first segment of each tile, then n_seg
+  const u64* tile_meta;    // [0] tiles, [1] records
+  const ah_result* hres;   // the sites' result: no pairing on an overflow
   int key_bits;            // bits of pos << 2 | strand-primer
   TmJob tj;
   const PairTab* ptabs;
-  u32* pcf;                // long segments: kept fwd- / rev- minus sites up to
+  u32* pcf;                // long tiles: kept fwd- / rev- minus sites up to
   u32* pcr;                // each record (inclusive), by record index
   u32* cnt;                // amplicons each record leads (0: not a leader)
   uint4* rng;              // a leader's minus ranges, one per record
-  u64* lb;                 // look-back words, one per segment (cleared before the scan)
+  u64* lb;                 // look-back words, one per tile (cleared before the scan)
   ah_amplicon* amp;
   u64 acap;
   ah_result* ares;
@@ -1529,45 +1561,9 @@ __device__ __forceinline__ u32 seg_count(const C* pc, uint2 r) {
   return (r.y ? (u32)pc[r.y - 1] : 0u) - (r.x ? (u32)pc[r.x - 1] : 0u);
 }
 
-// One wave per segment: the segment kernels run workgroups of one wave, so
-// that a segment of a few sites does not hold three idle waves (and their
-// registers), and every segment of the query is resident at once.
-constexpr u32 kSegBlock = 64;
-
-
-// Leaders of the sorted segment at records base .. base + m: the amplicons
-// each starts (cnt) and its minus ranges (rng: fwd-primer x, y and
-// rev-primer z, w, the same for both + sites of a group, which share the
-// position); returns the segment's total.  The last record a lane handled
-// leaves its count and ranges in c_last / r_last (for a segment of at most
-// one record per lane, this lane's own).
-template <class PosF, class KindF, class C>
-__device__ __forceinline__ u64 seg_leaders(const SegArgs& A, const PairTab& pt, u64 base, u32 m,
-                                           const PosF& P, const KindF& K, const C* pcf,
-                                           const C* pcr, u32& c_last, uint4& r_last) {
-  u64 sum = 0;
-  c_last = 0;
-  r_last = make_uint4(0u, 0u, 0u, 0u);
-  for (u32 i = threadIdx.x; i < m; i += kSegBlock) {
-    u32 c = 0;
-    const u32 k = K(i), pos = P(i);
-    if (plus_kind(k) && !(i > 0 && plus_kind(K(i - 1)) && P(i - 1) == pos)) {
-      const u32 ng = (i + 1 < m && plus_kind(K(i + 1)) && P(i + 1) == pos) ? 2u : 1u;
-      const uint2 rf = seg_range(P, m, pos, pt.lf, pt), rr = seg_range(P, m, pos, pt.lr, pt);
-      c = ng * (seg_count(pcf, rf) + seg_count(pcr, rr));
-      r_last = make_uint4(rf.x, rf.y, rr.x, rr.y);
-      A.rng[base + i] = r_last;
-    }
-    A.cnt[base + i] = c;
-    c_last = c;
-    sum += c;
-  }
-  return wave_sum(sum);
-}
-
-// Look-back words: (state << 62) | value, state 1: the segment's own
-// amplicons, 2: those of it and every earlier segment; kLbErr marks a
-// prefix that a wait gave up on.
+// Look-back words: (state << 62) | value, state 1: the tile's own amplicons,
+// 2: those of it and every earlier tile; kLbErr marks a prefix that a wait
+// gave up on.
 constexpr u64 kLbAgg = 1ull << 62, kLbIncl = 2ull << 62, kLbErr = 1ull << 61;
 constexpr u64 kLbVal = (1ull << 61) - 1ull;
 constexpr u32 kLbPolls = 1u << 20;  // polls of one window before a wait gives up
@@ -1579,12 +1575,13 @@ __device__ __forceinline__ void lb_store(u64* p, u64 v) {
   __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// Amplicons of segments 0 .. s - 1, with kLbErr set when a wait gave up
-// (every lane returns the same).  Segment s publishes its own count `agg`
-// first, then reads the words of the 64 segments before the ones it has
+// Amplicons of tiles 0 .. s - 1, with kLbErr set when a wait gave up (every
+// lane returns the same; one wave calls it).  Tile s publishes its own count
+// `agg` first, then reads the words of the 256 tiles before the ones it has
 // summed at once, back to the nearest inclusive word, and publishes its
-// inclusive count.  A workgroup waits only on lower segments, whose
-// workgroups were dispatched before it.
+// inclusive count.  A workgroup waits only on lower tiles, whose workgroups
+// were dispatched before it.
+constexpr u32 kLbWords = 4;  // words a lane reads at once: a window of 256 tiles
 __device__ __forceinline__ u64 seg_lookback(u64* lb, u32 s, u64 agg) {
   const u32 lane = threadIdx.x & 63u;
   if (s == 0) {
@@ -1593,37 +1590,54 @@ __device__ __forceinline__ u64 seg_lookback(u64* lb, u32 s, u64 agg) {
   }
   if (lane == 0) lb_store(&lb[s], kLbAgg | agg);
   u64 acc = 0, err = 0;
-  long long j = (long long)s - 1;
+  long long j = (long long)s - 1;  // the nearest tile not summed yet
   u32 polls = 0;
   for (;;) {
-    const long long idx = j - (long long)lane;
-    const u64 w = idx >= 0 ? lb_load(&lb[idx]) : kLbIncl;
-    const u64 incl = __ballot((w >> 62) == 2u);
-    const u32 first = incl ? (u32)__ffsll((long long)incl) - 1u : 64u;  // lane 0 reads j
-    const u64 need = first >= 63u ? ~0ull : (2ull << first) - 1ull;
-    const u64 ready = __ballot((w >> 62) != 0u);
-    if ((ready & need) != need) {  // a word the sum needs is not published yet
+    u64 v[kLbWords];
+#pragma unroll
+    for (u32 q = 0; q < kLbWords; ++q) {
+      const long long idx = j - (long long)(64u * q + lane);
+      v[q] = idx >= 0 ? lb_load(&lb[idx]) : kLbIncl;
+    }
+    // the 64 nearest, then the next 64, ...: as far as every word is published
+    u32 done = 0;
+    bool found = false;
+#pragma unroll
+    for (u32 q = 0; q < kLbWords; ++q) {
+      if (found || done != q) continue;
+      const u64 w = v[q];
+      const u64 incl = __ballot((w >> 62) == 2u);
+      const u32 first = incl ? (u32)__ffsll((long long)incl) - 1u : 64u;  // lane 0: the nearest
+      const u64 need = first >= 63u ? ~0ull : (2ull << first) - 1ull;
+      if ((__ballot((w >> 62) != 0u) & need) != need) continue;  // not published yet
+      acc += wave_sum(lane <= first ? (w & kLbVal) : 0ull);
+      if (__ballot(lane <= first && (w & kLbErr) != 0ull)) err = kLbErr;
+      found = first < 64u;
+      ++done;
+    }
+    if (found) break;
+    j -= 64ll * done;
+    if (done == 0) {
       if (++polls > kLbPolls) {
         err = kLbErr;
         break;
       }
       __builtin_amdgcn_s_sleep(2);
-      continue;
     }
-    acc += wave_sum(lane <= first ? (w & kLbVal) : 0ull);
-    if (__ballot(lane <= first && (w & kLbErr) != 0ull)) err = kLbErr;
-    if (first < 64u) break;
-    j -= 64;
   }
   if (lane == 0) lb_store(&lb[s], kLbIncl | err | ((acc + agg) & kLbVal));
   return acc | err;
 }
 
-// Bitonic sort of a[0 .. n2) (n2 a power of two) by the one-wave workgroup.
+// Bitonic sort of a[0 .. n2) (n2 a power of two) by a workgroup of kB threads.
+// The pairs of a wave with a stride of at most 64 lie in 128 keys of its own:
+// only longer strides need the whole workgroup.
+template <int kB>
 __device__ __forceinline__ void lds_bitonic(u64* a, u32 n2) {
   for (u32 k = 2; k <= n2; k <<= 1)
     for (u32 j = k >> 1; j > 0; j >>= 1) {
-      for (u32 p = threadIdx.x; p < n2 / 2; p += kSegBlock) {
+      if (kB > 64 && (j >= 64u || j == k >> 1) && n2 > 128u) __syncthreads();
+      for (u32 p = threadIdx.x; p < n2 / 2; p += kB) {
         const u32 i = ((p & ~(j - 1u)) << 1) | (p & (j - 1u));  // bit j of i clear
         const u32 l = i | j;
         const u64 x = a[i], y = a[l];
@@ -1632,12 +1646,34 @@ __device__ __forceinline__ void lds_bitonic(u64* a, u32 n2) {
           a[l] = x;
         }
       }
-      __syncthreads();
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      __builtin_amdgcn_wave_barrier();
     }
+  __syncthreads();
 }
 
-constexpr u32 kSegIdxBits = 10;  // record index inside a sorted LDS key
-static_assert((1u << kSegIdxBits) == kSegLds, "LDS keys carry the record index");
+// Exclusive prefix of one value per thread over a workgroup of kB threads;
+// tmp: kB / 64 entries of LDS.
+template <int kB>
+__device__ __forceinline__ u64 tail_scan(u64 v, u64* tmp, u64& total) {
+  const u64 incl = wave_incl_scan(v);
+  if (kB == 64) {
+    total = __shfl(incl, 63, 64);
+    return incl - v;
+  }
+  const u32 w = threadIdx.x >> 6;
+  if ((threadIdx.x & 63u) == 63u) tmp[w] = incl;
+  __syncthreads();
+  u64 before = 0;
+  total = 0;
+#pragma unroll
+  for (u32 q = 0; q < kB / 64; ++q) {
+    before += q < w ? tmp[q] : 0ull;
+    total += tmp[q];
+  }
+  __syncthreads();
+  return before + incl - v;
+}
 
 // Writes the amplicons leader i starts, from slot `at` on (below acap), in
 // (end, orient) order: up to four lists (each + site of the group with the
@@ -1692,7 +1728,7 @@ __device__ __forceinline__ void seg_write(const SegArgs& A, const PairTab& pt, c
 }
 
 // The amplicon result from the query's total (kLbErr: a look-back wait gave
-// up, reported as AH_ERR_HIP), written by the last segment's workgroup.
+// up, reported as AH_ERR_HIP), written by the last tile's workgroup.
 __device__ __forceinline__ void seg_result(const SegArgs& A, u64 total) {
   const u64 n = total & kLbVal;
   A.ares->required = n;
@@ -1701,32 +1737,88 @@ __device__ __forceinline__ void seg_result(const SegArgs& A, u64 total) {
   A.ares->reserved = 0;
 }
 
-// Segment blockIdx.x: canonical order, Tm, leaders, amplicons.
-template <bool kExact>
-__global__ __launch_bounds__(kSegBlock) void k_seg_tail(SegArgs A) {
-  __shared__ u64 keys[kSegLds];  // also the long path's digit counters
-  __shared__ u32 spos[kSegLds];
-  __shared__ unsigned short pcf[kSegLds], pcr[kSegLds];
-  __shared__ unsigned char kind[kSegLds];
+// One stable LSD pass of m records by digit(record) (below 256), src -> dst, by
+// the workgroup; run: 256 LDS counters, wcnt: 256 per wave.
+template <int kB, class DigitF>
+__device__ __forceinline__ void tail_pass(const ah_hit* src, ah_hit* dst, u32 m, u32* run, u32* wcnt,
+                                          u64* tmp, const DigitF& digit) {
+  constexpr u32 kW = kB / 64, kOwn = 256 / kB;
+  const u32 t = threadIdx.x, lane = t & 63u, w = t >> 6;
+#pragma unroll
+  for (u32 q = 0; q < kOwn; ++q) run[kOwn * t + q] = 0;
+  __syncthreads();
+  for (u32 i = t; i < m; i += kB) atomicAdd(&run[digit(src[i])], 1u);
+  __syncthreads();
+  {  // exclusive prefix of the counts: thread t owns digits kOwn t ..
+    u32 c[kOwn];
+    u64 own = 0, all;
+#pragma unroll
+    for (u32 q = 0; q < kOwn; ++q) {
+      c[q] = run[kOwn * t + q];
+      own += c[q];
+    }
+    u64 at = tail_scan<kB>(own, tmp, all);
+#pragma unroll
+    for (u32 q = 0; q < kOwn; ++q) {
+      run[kOwn * t + q] = (u32)at;
+      at += c[q];
+    }
+  }
+  for (u32 r0 = 0; r0 < m; r0 += kB) {
+    for (u32 q = t; q < 256u * kW; q += kB) wcnt[q] = 0;
+    __syncthreads();
+    const u32 i = r0 + t;
+    const bool valid = i < m;
+    ah_hit h{};
+    u32 d = 0;
+    if (valid) {
+      h = src[i];
+      d = digit(h);
+    }
+    // this lane's rank among the wave's lanes with the same digit
+    u64 peers = __ballot(valid);
+    for (int bit = 0; bit < 8; ++bit) {
+      const bool on = (d >> bit) & 1u;
+      const u64 bal = __ballot(valid && on);
+      peers &= on ? bal : ~bal;
+    }
+    const u32 rank = (u32)__popcll(peers & ((1ull << lane) - 1ull));
+    if (valid && rank == 0) wcnt[256u * w + d] = (u32)__popcll(peers);
+    __syncthreads();
+    if (valid) {
+      u32 at = run[d] + rank;
+      for (u32 q = 0; q < w; ++q) at += wcnt[256u * q + d];
+      dst[at] = h;
+    }
+    __syncthreads();
+#pragma unroll
+    for (u32 e = 0; e < kOwn; ++e)
+      for (u32 q = 0; q < kW; ++q) run[kOwn * t + e] += wcnt[256u * q + kOwn * t + e];
+    __syncthreads();
+  }
+}
+
+// Tile blockIdx.x of the staged records: canonical order, Tm, leaders, amplicons.
+template <bool kExact, int kB, int kCap>
+__global__ __launch_bounds__(kB) void k_query_tail(SegArgs A) {
+  constexpr u32 kIdxBits = kCap == 4096 ? 12 : 10;  // record index inside a sorted key
+  static_assert((1u << kIdxBits) == kCap, "LDS keys carry the record index");
+  __shared__ u64 keys[kCap];  // also the long path's digit counters
+  __shared__ unsigned short pcf[kCap], pcr[kCap];
+  __shared__ unsigned char kind[kCap];
   __shared__ NnFix s_nn[16];
-  __shared__ PrimerTab s_tab[2];  // the pair's primer tables, read throughout the Tm
-  __shared__ int s_best[kSegBlock];  // the best pairing of each lane's site
-  const u32 t = threadIdx.x, s = blockIdx.x;
-  // the segment's constants, loaded together: its sites, first slot, pair
-  // tables and genome (every site of segment s is on genome s mod n)
+  __shared__ int s_best[kB];  // the best pairing of each lane's site
+  __shared__ u64 tmp[kB / 64];
+  __shared__ u64 s_before;
+  const u32 t = threadIdx.x, lane = t & 63u, wv = t >> 6, b = blockIdx.x;
   const int status = A.hres->status;
-  const u32 m = A.seg_cnt[s];
-  const u64 base = A.seg_off[s];
-  const u32 pair = s / A.n_genomes, g = s % A.n_genomes;
-  const PairTab pt = A.ptabs[pair];
-  const u64 S = ((u64)A.tj.len[g] + 31) >> 5, wbase = A.tj.word_off[g];
-  static_assert(sizeof(PrimerTab) % 4 == 0, "primer tables copy as words");
-  for (u32 i = t; i < 2 * sizeof(PrimerTab) / 4; i += kSegBlock)
-    ((u32*)s_tab)[i] = ((const u32*)(A.tj.tabs + 2 * pair))[i];
-  tm_tables(s_nn);  // its barrier also covers the copy
+  const u64 nt = A.tile_meta[0], n = A.tile_meta[1];
+  const u32 sa = A.tile_seg[b], sb = A.tile_seg[b + 1];  // loaded with the count: read below nt only
+  const u64 base = A.tile_base[b], base1 = A.tile_base[b + 1];
+  tm_tables(s_nn);
   const bool sites_ok = status == AH_OK;
   if (!sites_ok) {  // the sites overflowed: the pairing needs all of them
-    if (s == 0 && t == 0) {
+    if (b == 0 && t == 0) {
       A.ares->count = 0;
       A.ares->required = 0;
       A.ares->status = AH_ERR_OVERFLOW;
@@ -1735,142 +1827,84 @@ __global__ __launch_bounds__(kSegBlock) void k_seg_tail(SegArgs A) {
     // The sites found still go out in canonical order with their Tm, as the
     // separate calls write them, when they fit (a full candidate list left
     // them incomplete); past the capacity none were staged.
-    if (m == 0 || A.seg_off[A.n_seg] > A.hcap) return;
+    if (n > A.hcap) return;
   }
+  if (b >= nt) return;
+  const u32 m = (u32)(base1 - base);
   if (m == 0) {
-    const u64 before = seg_lookback(A.lb, s, 0ull);
-    if (s + 1 == A.n_seg && t == 0) seg_result(A, before);
+    if (sites_ok && wv == 0) {
+      const u64 before = seg_lookback(A.lb, b, 0ull);
+      if (b + 1 == nt && t == 0) seg_result(A, before);
+    }
     return;
   }
-  const bool tiny = m <= kSegBlock, small = m <= kSegLds;
+  const bool small = m <= (u32)kCap;
   ah_hit* o = A.out + base;
-  if (tiny) {
-    // one site per lane: a bitonic network over the wave's registers, then
-    // each lane takes the record of its sorted place from the lane that
-    // loaded it
-    ah_hit h{};
-    u64 key = ~0ull;
-    if (t < m) {
-      h = A.staged[base + t];
-      key = (seg_key(h) << 6) | t;
-    }
-    for (u32 k = 2; k <= kSegBlock; k <<= 1)
-      for (u32 j = k >> 1; j > 0; j >>= 1) {
-        const u64 y = __shfl_xor(key, j, 64);
-        const bool keep_min = ((t & j) == 0u) == ((t & k) == 0u);
-        key = keep_min ? (y < key ? y : key) : (y > key ? y : key);
-      }
-    u32 hv[4];
-    __builtin_memcpy(hv, &h, sizeof hv);
-    const int from = (int)(key & 63u);
-#pragma unroll
-    for (int q = 0; q < 4; ++q) hv[q] = __shfl(hv[q], from, 64);
-    ah_hit r;
-    __builtin_memcpy(&r, hv, sizeof r);
-    const float tmv = tm_wave<kExact>(A.tj, r, t < m, S, wbase, s_nn, s_tab, s_best);
-    if (t < m) {
-      r.tm = tmv;
-      o[t] = r;
-      spos[t] = r.pos;
-      kind[t] = (unsigned char)seg_kind(r, pt);
-    }
-  } else if (small) {
-    // keys with the record index below them, padded to a power of two
-    u32 n2 = 1;
+  const int kb = A.key_bits;
+  auto local = [&](const ah_hit& h) { return (u32)h.pair * A.n_genomes + h.genome - sa; };
+  if (small) {
+    u32 n2 = 2;
     while (n2 < m) n2 <<= 1;
-    for (u32 e = t; e < n2; e += kSegBlock)
-      keys[e] = e < m ? (seg_key(A.staged[base + e]) << kSegIdxBits) | e : ~0ull;
+    for (u32 e = t; e < n2; e += kB) {
+      u64 key = ~0ull;
+      if (e < m) {
+        const ah_hit h = A.staged[base + e];
+        key = ((((u64)local(h) << kb) | seg_key(h)) << kIdxBits) | e;
+      }
+      keys[e] = key;
+    }
     __syncthreads();
-    lds_bitonic(keys, n2);
+    lds_bitonic<kB>(keys, n2);
   } else {
-    // stable LSD passes, an odd number, staging <-> output
-    u32* hist = (u32*)keys;  // [256] digit counts, then first slots
-    const int bits = A.key_bits;
-    int np = (bits + 7) / 8;
+    int np = (kb + 32 - __builtin_clz((sb - sa) | 1u) + 7) / 8;
     if ((np & 1) == 0) ++np;
-    const int D = (bits + np - 1) / np;
-    const u32 mask = (1u << D) - 1u;
-    ah_hit* src = A.staged + base;
-    ah_hit* dst = A.out + base;
-    const u32 lane = t & 63u;
+    ah_hit *src = A.staged + base, *dst = o;
     for (int p = 0; p < np; ++p) {
-      const int shift = p * D;
-#pragma unroll
-      for (u32 q = 0; q < 4; ++q) hist[q * 64 + t] = 0;
-      __syncthreads();
-      for (u32 i = t; i < m; i += kSegBlock)
-        atomicAdd(&hist[(u32)(seg_key(src[i]) >> shift) & mask], 1u);
-      __syncthreads();
-      {  // exclusive prefix of the 256 counts: lane t owns digits 4t .. 4t + 3
-        u32 c[4];
-        u64 own = 0;
-#pragma unroll
-        for (u32 q = 0; q < 4; ++q) {
-          c[q] = hist[4 * t + q];
-          own += c[q];
-        }
-        u64 at = wave_incl_scan(own) - own;
-#pragma unroll
-        for (u32 q = 0; q < 4; ++q) {
-          hist[4 * t + q] = (u32)at;
-          at += c[q];
-        }
-      }
-      __syncthreads();
-      for (u32 r0 = 0; r0 < m; r0 += kSegBlock) {
-        const u32 i = r0 + t;
-        const bool valid = i < m;
-        ah_hit h{};
-        u32 d = 0;
-        if (valid) {
-          h = src[i];
-          d = (u32)(seg_key(h) >> shift) & mask;
-        }
-        // this lane's rank among the lanes with the same digit
-        u64 peers = __ballot(valid);
-        for (int bit = 0; bit < D; ++bit) {
-          const bool on = (d >> bit) & 1u;
-          const u64 bal = __ballot(valid && on);
-          peers &= on ? bal : ~bal;
-        }
-        const u32 rank = (u32)__popcll(peers & ((1ull << lane) - 1ull));
-        if (valid) dst[hist[d] + rank] = h;
-        __syncthreads();
-        if (valid && rank == 0) hist[d] += (u32)__popcll(peers);
-        __syncthreads();
-      }
+      tail_pass<kB>(src, dst, m, (u32*)keys, (u32*)keys + 256, tmp, [&](const ah_hit& h) {
+        const u64 key = ((u64)local(h) << kb) | seg_key(h);
+        return 8 * p < 64 ? (u32)(key >> (8 * p)) & 255u : 0u;
+      });
       ah_hit* x = src;
       src = dst;
       dst = x;
     }
-    // src == A.out + base: the passes are odd in number
+    // src == o: the passes are odd in number
   }
   // the Tm of every site, written with the record to its place
-  if (!tiny)
-    for (u32 r0 = 0; r0 < m; r0 += kSegBlock) {  // the whole wave, 64 records at a time
-      const u32 i = r0 + t;
-      ah_hit h{};
-      if (i < m) h = small ? A.staged[base + (u32)(keys[i] & (kSegLds - 1u))] : o[i];
-      const float tmv = tm_wave<kExact>(A.tj, h, i < m, S, wbase, s_nn, s_tab, s_best);
-      if (i < m) {
-        h.tm = tmv;
-        o[i] = h;
-        if (small) {
-          spos[i] = h.pos;
-          kind[i] = (unsigned char)seg_kind(h, pt);
-        }
-      }
+  for (u32 r0 = wv * 64u; r0 < m; r0 += kB) {  // the whole wave, 64 records at a time
+    const u32 i = r0 + lane;
+    ah_hit h{};
+    if (i < m) h = small ? A.staged[base + (u32)(keys[i] & (kCap - 1u))] : o[i];
+    const u32 g = h.genome, pair = h.pair;  // lanes past the tile: 0, in range
+    const u64 S = ((u64)A.tj.len[g] + 31) >> 5, wbase = A.tj.word_off[g];
+    const float tmv = tm_wave<kExact>(A.tj, h, i < m, S, wbase, s_nn, &A.tj.tabs[pair * 2u],
+                                      s_best + wv * 64u);
+    if (i < m) {
+      h.tm = tmv;
+      o[i] = h;
+      if (small) kind[i] = (unsigned char)seg_kind(h, A.ptabs[pair]);
     }
+  }
   __syncthreads();
   if (!sites_ok) return;  // the sites are in place; no pairing
+  // a site's position, kind, and its segment's records [lo, hi) in the tile
+  auto pos_of = [&](u32 i) {
+    return small ? (u32)((keys[i] >> (kIdxBits + 2)) & ((1ull << (kb - 2)) - 1ull)) : o[i].pos;
+  };
+  auto kind_of = [&](u32 i) {
+    return small ? (u32)kind[i] : seg_kind(o[i], A.ptabs[o[i].pair]);
+  };
+  auto seg_of = [&](u32 i) {  // segment number
+    return sa + (small ? (u32)(keys[i] >> (kIdxBits + kb)) : local(o[i]));
+  };
   // kept fwd- (low half) and rev- (high half) minus sites up to each record
   u64 carry = 0;
-  for (u32 r0 = 0; r0 < m; r0 += kSegBlock) {
+  for (u32 r0 = 0; r0 < m; r0 += kB) {
     const u32 i = r0 + t;
-    const u32 k = i < m ? (small ? (u32)kind[i] : seg_kind(o[i], pt)) : 0u;
+    const u32 k = i < m ? kind_of(i) : 0u;
     const u64 v = (k == 6u ? 1ull : 0ull) | (k == 7u ? 1ull << 32 : 0ull);
-    const u64 incl = wave_incl_scan(v);
-    const u64 inc = carry + incl;
+    u64 all;
+    const u64 inc = carry + tail_scan<kB>(v, tmp, all) + v;
     if (i < m) {
       if (small) {
         pcf[i] = (unsigned short)(inc & 0xffffffffull);
@@ -1880,41 +1914,82 @@ __global__ __launch_bounds__(kSegBlock) void k_seg_tail(SegArgs A) {
         A.pcr[base + i] = (u32)(inc >> 32);
       }
     }
-    carry += __shfl(incl, 63, 64);
+    carry += all;
   }
   __syncthreads();
-  u64 sum;
-  u32 c_own;
-  uint4 r_own;
-  if (small)
-    sum = seg_leaders(A, pt, base, m, [&](u32 i) { return spos[i]; },
-                      [&](u32 i) { return (u32)kind[i]; }, pcf, pcr, c_own, r_own);
-  else
-    sum = seg_leaders(A, pt, base, m, [&](u32 i) { return o[i].pos; },
-                      [&](u32 i) { return seg_kind(o[i], pt); }, A.pcf + base, A.pcr + base,
-                      c_own, r_own);
-  const u64 before = seg_lookback(A.lb, s, sum);
-  if (s + 1 == A.n_seg && t == 0) seg_result(A, (before & kLbErr) | ((before & kLbVal) + sum));
+  auto sites_in = [&](uint2 r, bool rev) -> u32 {  // kept minus sites of records [r.x, r.y)
+    if (r.x >= r.y) return 0u;
+    if (small) {
+      const unsigned short* pc = rev ? pcr : pcf;
+      return (u32)pc[r.y - 1] - (r.x ? (u32)pc[r.x - 1] : 0u);
+    }
+    const u32* pc = (rev ? A.pcr : A.pcf) + base;
+    return pc[r.y - 1] - (r.x ? pc[r.x - 1] : 0u);
+  };
+  // Leaders: the amplicons each starts (cnt) and its minus ranges (rng:
+  // fwd-primer x, y and rev-primer z, w, the same for both + sites of a group,
+  // which share the position).
+  u64 sum = 0;
+  for (u32 i = t; i < m; i += kB) {
+    u32 c = 0;
+    if (plus_kind(kind_of(i))) {
+      const u32 s = seg_of(i), pos = pos_of(i);
+      const u32 lo = (u32)(A.seg_off[s] - base), hi = (u32)(A.seg_off[s + 1] - base);
+      if (!(i > lo && plus_kind(kind_of(i - 1)) && pos_of(i - 1) == pos)) {
+        const PairTab pt = A.ptabs[s / A.n_genomes];
+        const u32 ng = (i + 1 < hi && plus_kind(kind_of(i + 1)) && pos_of(i + 1) == pos) ? 2u : 1u;
+        auto at = [&](u32 j) { return pos_of(lo + j); };
+        uint2 rf = seg_range(at, hi - lo, pos, pt.lf, pt), rr = seg_range(at, hi - lo, pos, pt.lr, pt);
+        rf.x += lo; rf.y += lo; rr.x += lo; rr.y += lo;
+        c = ng * (sites_in(rf, false) + sites_in(rr, true));
+        if (c) A.rng[base + i] = make_uint4(rf.x, rf.y, rr.x, rr.y);
+      }
+    }
+    A.cnt[base + i] = c;
+    sum += c;
+  }
+  {
+    u64 all;
+    (void)tail_scan<kB>(sum, tmp, all);
+    sum = all;
+  }
+  if (wv == 0) {
+    const u64 before = seg_lookback(A.lb, b, sum);
+    if (b + 1 == nt && t == 0) seg_result(A, (before & kLbErr) | ((before & kLbVal) + sum));
+    if (t == 0) s_before = before;
+  }
+  __syncthreads();
+  const u64 before = s_before;
   if ((before & kLbErr) || sum == 0 || before >= A.acap) return;
-  __syncthreads();  // this wave's counts and ranges are in place
   u64 at0 = before;
-  for (u32 r0 = 0; r0 < m; r0 += kSegBlock) {
+  for (u32 r0 = 0; r0 < m; r0 += kB) {
     const u32 i = r0 + t;
-    // one record per lane: the count and ranges are still in this lane's registers
-    const u32 c = tiny ? c_own : (i < m ? A.cnt[base + i] : 0u);
-    const u64 incl = wave_incl_scan(c);
-    const u64 at = at0 + incl - c;
-    at0 += __shfl(incl, 63, 64);
+    const u32 c = i < m ? A.cnt[base + i] : 0u;  // written by this thread
+    u64 all;
+    const u64 at = at0 + tail_scan<kB>(c, tmp, all);
+    at0 += all;
     if (c && at < A.acap) {
-      const uint4 g = tiny ? r_own : A.rng[base + i];
-      if (small)
-        seg_write(A, pt, o, base, i, m, at, A.acap, A.amp, [&](u32 j) { return spos[j]; },
-                  [&](u32 j) { return (u32)kind[j]; }, g);
-      else
-        seg_write(A, pt, o, base, i, m, at, A.acap, A.amp, [&](u32 j) { return o[j].pos; },
-                  [&](u32 j) { return seg_kind(o[j], pt); }, g);
+      const u32 s = seg_of(i);
+      seg_write(A, A.ptabs[s / A.n_genomes], o, base, i, (u32)(A.seg_off[s + 1] - base), at, A.acap,
+                A.amp, pos_of, kind_of, A.rng[base + i]);
     }
   }
+}
+
+// First record of each segment from the segments' counts (the exclusive prefix,
+// n_seg + 1 entries), for more segments than the segmented emit sums itself.
+// (The counts lie by genome, then pair; segments are numbered by pair, then genome.)
+__global__ __launch_bounds__(kSmallBlock) void k_seg_prefix(const u32* __restrict__ cnt, u32 n_seg,
+                                                            u32 n_genomes, u64* __restrict__ off) {
+  const u32 n_pairs = n_seg / n_genomes;
+  const u64 upto = run_prefix(
+      n_seg,
+      [&](u32 s) {
+        const u32 q = n_pairs == 1u ? 0u : s / n_genomes;
+        return cnt[(u64)(s - q * n_genomes) * n_pairs + q];
+      },
+      [&](u32 s, u64 at) { off[s] = at; });
+  if (threadIdx.x == 0 && blockIdx.x + 1 == gridDim.x) off[n_seg] = upto;
 }
 
 // ----------------------------------------------------- amplicon FASTA ----
@@ -2494,9 +2569,9 @@ hipError_t launch_tile_prefix_small(const uint32_t* len, uint32_t n, uint32_t ti
                                     uint64_t* prefix, ah_result* res, hipStream_t st,
                                     uint32_t* zero, uint32_t n_zero, uint64_t* zero64,
                                     uint32_t n_zero64) {
-  k_tile_prefix_small<<<1, kSmallBlock, 0, st>>>(len, n, tile_words, (u64*)prefix, res, zero,
-                                                 zero ? n_zero : 0u, (u64*)zero64,
-                                                 zero64 ? n_zero64 : 0u);
+  k_tile_prefix_small<<<(n + kRun - 1) / kRun, kSmallBlock, 0, st>>>(
+      len, n, tile_words, (u64*)prefix, res, zero, zero ? n_zero : 0u, (u64*)zero64,
+      zero64 ? n_zero64 : 0u);
   return hipGetLastError();
 }
 
@@ -2569,6 +2644,12 @@ hipError_t launch_sort_tm_mark(ah_hit* staged, ah_hit* out, const uint64_t* n_de
   return hipGetLastError();
 }
 
+hipError_t launch_seg_prefix(const SegBuffers& sg, hipStream_t st) {
+  k_seg_prefix<<<(sg.n_seg + kRun - 1) / kRun, kSmallBlock, 0, st>>>(sg.cnt, sg.n_seg, sg.n_genomes,
+                                                                  (u64*)sg.off);
+  return hipGetLastError();
+}
+
 hipError_t launch_seg_tail(ah_hit* staged, ah_hit* out, uint64_t hcap, const SegBuffers& sg,
                            const ah_result* hres, int key_bits, const ah_genomes& g,
                            const PrimerTab* tm_tabs, uint32_t n_pairs, const PairTab* pair_tabs,
@@ -2577,10 +2658,12 @@ hipError_t launch_seg_tail(ah_hit* staged, ah_hit* out, uint64_t hcap, const Seg
   SegArgs A;
   A.staged = staged;
   A.out = out;
-  A.seg_cnt = sg.cnt;
   A.seg_off = (const u64*)sg.off;
   A.n_seg = sg.n_seg;
   A.n_genomes = sg.n_genomes;
+  A.tile_base = (const u64*)sg.tile_base;
+  A.tile_seg = sg.tile_seg;
+  A.tile_meta = (const u64*)sg.tile_meta;
   A.hres = hres;
   A.key_bits = key_bits;
   A.tj = TmJob{(const uint2*)g.words, g.nmask, (const u64*)g.word_off, g.len, tm_tabs, g.n, n_pairs};
@@ -2594,11 +2677,17 @@ hipError_t launch_seg_tail(ah_hit* staged, ah_hit* out, uint64_t hcap, const Seg
   A.acap = acap;
   A.hcap = hcap;
   A.ares = ares;
-  const u32 grid = sg.n_seg > 0 ? sg.n_seg : 1u;
-  if (exact)
-    k_seg_tail<true><<<grid, kSegBlock, 0, st>>>(A);
-  else
-    k_seg_tail<false><<<grid, kSegBlock, 0, st>>>(A);
+  if (sg.wide) {
+    if (exact)
+      k_query_tail<true, 256, 4096><<<sg.n_tiles, 256, 0, st>>>(A);
+    else
+      k_query_tail<false, 256, 4096><<<sg.n_tiles, 256, 0, st>>>(A);
+  } else {
+    if (exact)
+      k_query_tail<true, 64, 1024><<<sg.n_tiles, 64, 0, st>>>(A);
+    else
+      k_query_tail<false, 64, 1024><<<sg.n_tiles, 64, 0, st>>>(A);
+  }
   return hipGetLastError();
 }
 
@@ -2680,7 +2769,7 @@ hipError_t launch_remap(ah_hit* hits, const ah_result* hres, ah_amplicon* amp, c
 }
 
 hipError_t launch_zero_u64(uint64_t* p, uint32_t n, hipStream_t st) {
-  k_zero_u64<<<1, 64, 0, st>>>((u64*)p, n);
+  k_zero_u64<<<n <= kBlock ? 1u : std::min(n / kBlock, 256u), kBlock, 0, st>>>((u64*)p, n);
   return hipGetLastError();
 }
 

@@ -46,7 +46,7 @@
 // positions mismatch every primer position), AH_WAVE (1: wave mode, below),
 // AH_QUAD_ONE_PAIR (1: the four patterns of every candidate record belong to
 // one primer pair), AH_TILE_COUNT (1: in tile mode the filter takes the exact
-// count).
+// count), AH_PAIRS (primer pairs of the set).
 
 typedef unsigned int u32;
 typedef unsigned long long u64;
@@ -271,11 +271,51 @@ __device__ u32 ah_verify_one(const AhCtx& c, W w, u32 t, u32 p, u32 cand, AhHitR
 // Generated: the primer pair of pattern p.
 __device__ u32 ah_pat_pair(u32 p);
 
+// Where a segment's count and fill counter lie: by genome, then pair, so that the
+// pairs of one genome share a cache line rather than the genomes of one pair
+// (a few pairs of a panel have most of its sites, and device atomics to one
+// line serialise): the count over a 64-pair panel's 430,000 sites took 822 us by
+// pair, 682 us by genome.
+__device__ __forceinline__ u32 ah_seg_slot(u32 pair, u32 genome) { return genome * AH_PAIRS + pair; }
+
+// Reserves `found` places in segment sg's count: the first of them + 1, or 0 for
+// none.  Device atomics to one cache line (32 counts) serialise, at about 20 ns
+// each, and a wave's candidates often share a segment (a pair with many sites
+// on a genome): where many lanes have sites, the lanes of each segment take
+// their places with one atomic.
+__device__ __forceinline__ u32 ah_seg_place(u32* __restrict__ seg_cnt, u32 sg, u32 found) {
+  u64 todo = __ballot(found != 0u);
+  if (__popcll(todo) <= 8) return found ? atomicAdd(&seg_cnt[sg], found) + 1u : 0u;
+  const u32 lane = threadIdx.x & 63u;
+  const u64 many = __ballot(found > 1u);
+  u32 lead = lane, rank = 0, sum = found;  // the segment's first lane, places before this lane's, all
+  while (todo) {
+    const u32 l = __ffsll((unsigned long long)todo) - 1u;
+    const u64 same = __ballot(sg == (u32)__builtin_amdgcn_readlane((int)sg, (int)l)) & todo;
+    todo &= ~same;
+    u32 r = (u32)__popcll(same & ((1ull << lane) - 1ull)), a = (u32)__popcll(same);
+    for (u64 x = same & many; x; x &= x - 1) {  // lanes with more than one site
+      const u32 k = __ffsll((unsigned long long)x) - 1u;
+      const u32 more = (u32)__builtin_amdgcn_readlane((int)found, (int)k) - 1u;
+      r += k < lane ? more : 0u;
+      a += more;
+    }
+    if ((same >> lane) & 1ull) {
+      lead = l;
+      rank = r;
+      sum = a;
+    }
+  }
+  u32 first = 0;
+  if (found && lead == lane) first = atomicAdd(&seg_cnt[sg], sum);
+  first = (u32)__shfl((int)first, (int)lead, 64);
+  return found ? first + rank + 1u : 0u;
+}
+
 // Exact count of candidate record `at` (the windows of its four patterns):
 // its sites go to cand_sites[at] and the running sums; with seg_cnt set they
-// are also counted per segment (pair, genome) at seg_cnt[pair * seg_n +
-// genome], and when every record's patterns share a pair (AH_QUAD_ONE_PAIR)
-// one device atomic per candidate reserves its sites' places in the segment:
+// are also counted per segment (pair, genome) at seg_cnt[ah_seg_slot], and when every record's patterns share a pair (AH_QUAD_ONE_PAIR)
+// its sites' places in the segment are reserved (ah_seg_place):
 // cand_sites[at] then keeps the first place + 1 (0: no sites) for the
 // segmented emit instead of the count.
 __device__ __forceinline__ void ah_verify_cand(const uint2* __restrict__ words,
@@ -295,12 +335,12 @@ __device__ __forceinline__ void ah_verify_cand(const uint2* __restrict__ words,
     if (m[q]) {
       const u32 f = ah_verify_one(c, c.gw + e.y, e.y, e.z + (u32)q, m[q], nullptr, 0, 0, false);
       if (!AH_QUAD_ONE_PAIR && seg_cnt && f)
-        atomicAdd(&seg_cnt[ah_pat_pair(e.z + (u32)q) * seg_n + e.x], f);
+        atomicAdd(&seg_cnt[ah_seg_slot(ah_pat_pair(e.z + (u32)q), e.x)], f);
       found += f;
       my_win += (u64)__popc(m[q]);
     }
   if (AH_QUAD_ONE_PAIR && seg_cnt)
-    cand_sites[at] = found ? atomicAdd(&seg_cnt[ah_pat_pair(e.z) * seg_n + e.x], found) + 1u : 0u;
+    cand_sites[at] = ah_seg_place(seg_cnt, ah_seg_slot(ah_pat_pair(e.z), e.x), found);
   else
     cand_sites[at] = found;
   my_sites += found;
@@ -739,14 +779,16 @@ extern "C" __global__ __launch_bounds__(AH_BLOCK) void ah_emit_kernel(
 
 // Segmented emit (the whole query in one call): the records go straight to
 // their segment (pair, genome), whose first slot is the sum of the sites of
-// the earlier segments (seg_cnt from the exact count, at most AH_SEG_MAX
-// segments), at the place inside it that the count reserved
-// (AH_QUAD_ONE_PAIR) or one taken here with a device atomic on
-// seg_fill[segment] (cleared before the filter).  The order inside a segment
-// is left to the segment sort that follows.  Workgroup 0 also writes the
-// segments' first slots (seg_off, n_seg + 1 entries), the result and the
-// candidate-list statistics, as the slice-order emit does.  Nothing is
-// written when the sites overflow the capacity.
+// the earlier segments (seg_cnt from the exact count; summed here for at most
+// AH_SEG_MAX segments, read from seg_off above), at the place inside it that
+// the count reserved (AH_QUAD_ONE_PAIR) or one taken here with a device atomic
+// on seg_fill[segment] (cleared before the filter).  The order inside a segment
+// is left to the sort that follows.  Workgroup 0 also writes the segments'
+// first slots (seg_off, n_seg + 1 entries) and the tail's tiles (T sites, T
+// from the count: about a thousand tiles, of at least 32 sites and at most t_n,
+// or the mean segment up to t_seg, so that few tiles hold no segment), the
+// result and the candidate-list statistics, as the slice-order emit does.
+// Nothing is written when the sites overflow the capacity.
 #define AH_SEG_MAX 4096
 extern "C" __global__ __launch_bounds__(AH_BLOCK) void ah_emit_seg_kernel(
     const uint2* __restrict__ words, const u32* __restrict__ nmask,
@@ -755,7 +797,8 @@ extern "C" __global__ __launch_bounds__(AH_BLOCK) void ah_emit_seg_kernel(
     const u32* __restrict__ slice_total, const u64* __restrict__ slice_win,
     const u32* __restrict__ cand_sites, const u32* __restrict__ seg_cnt, u32 n_seg, u32 seg_n,
     u64* __restrict__ seg_off, u32* __restrict__ seg_fill, AhHitRec* __restrict__ out, u64 cap,
-    AhResult* __restrict__ res, u64* __restrict__ cand_stat) {
+    AhResult* __restrict__ res, u64* __restrict__ cand_stat, u64* __restrict__ tile_base,
+    u32* __restrict__ tile_seg, u64* __restrict__ tile_meta, u32 t_n, u32 t_seg) {
   __shared__ u64 s_off[AH_SEG_MAX + 1];
   __shared__ u64 tmp[AH_BLOCK / 64];
   // this thread's first candidate, in flight while the slots are summed
@@ -769,28 +812,62 @@ extern "C" __global__ __launch_bounds__(AH_BLOCK) void ah_emit_seg_kernel(
     e0 = cands[2 * at0];
     mk0 = cands[2 * at0 + 1];
   }
-  // the segments' first slots: thread i sums a run of `per` segments
-  const u32 per = (n_seg + AH_BLOCK - 1) / AH_BLOCK;
-  const u32 s0 = threadIdx.x * per;
-  u32 v[AH_SEG_MAX / AH_BLOCK];
-  u64 mine = 0;
-#pragma unroll
-  for (u32 q = 0; q < AH_SEG_MAX / AH_BLOCK; ++q) {
-    v[q] = q < per && s0 + q < n_seg ? seg_cnt[s0 + q] : 0u;
-    mine += v[q];
-  }
+  // the segments' first slots: thread i sums a run of `per` segments; above
+  // AH_SEG_MAX they are in seg_off already
+  const bool big = n_seg > AH_SEG_MAX;
   u64 found;
-  u64 run = ah_block_scan(mine, tmp, &found);
+  if (big) {
+    found = seg_off[n_seg];
+  } else {
+    const u32 per = (n_seg + AH_BLOCK - 1) / AH_BLOCK;
+    const u32 s0 = threadIdx.x * per;
+    u32 v[AH_SEG_MAX / AH_BLOCK];
+    u64 mine = 0;
 #pragma unroll
-  for (u32 q = 0; q < AH_SEG_MAX / AH_BLOCK; ++q)
-    if (q < per && s0 + q < n_seg) {
-      s_off[s0 + q] = run;
-      run += v[q];
+    for (u32 q = 0; q < AH_SEG_MAX / AH_BLOCK; ++q) {
+      const u32 s = s0 + q;  // pair * seg_n + genome
+      v[q] = q < per && s < n_seg ? seg_cnt[AH_PAIRS == 1 ? s : ah_seg_slot(s / seg_n, s % seg_n)] : 0u;
+      mine += v[q];
     }
-  if (threadIdx.x == 0) s_off[n_seg] = found;
-  __syncthreads();
+    u64 run = ah_block_scan(mine, tmp, &found);
+#pragma unroll
+    for (u32 q = 0; q < AH_SEG_MAX / AH_BLOCK; ++q)
+      if (q < per && s0 + q < n_seg) {
+        s_off[s0 + q] = run;
+        run += v[q];
+      }
+    if (threadIdx.x == 0) s_off[n_seg] = found;
+    __syncthreads();
+  }
+  {
+    // The tail's tiles: tile b starts at the first segment at or past site b T.
+    // Workgroup 0 writes them with the segments' first slots; above AH_SEG_MAX
+    // segments the grid does.
+    u64 T = 32;
+    while (T < t_n && T * 1024 < found) T <<= 1;
+    while (T < t_seg && T * n_seg < found) T <<= 1;
+    const u64 nt = found ? (found + T - 1) / T : 1;
+    const u32 q0 = big ? blockIdx.x * AH_BLOCK + threadIdx.x : blockIdx.x ? n_seg + 1 : threadIdx.x;
+    for (u32 q = q0; q <= n_seg; q += big ? gridDim.x * AH_BLOCK : AH_BLOCK) {
+      const u64 o = big ? seg_off[q] : s_off[q];
+      const u64 prev = q ? (big ? seg_off[q - 1] : s_off[q - 1]) : 0;
+      if (!big) seg_off[q] = o;
+      if (found <= cap)
+        for (u64 b = q ? prev / T + 1 : 0; b * T <= o && b < nt; ++b) {
+          tile_base[b] = o;
+          tile_seg[b] = q;
+        }
+    }
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+      tile_meta[0] = nt;
+      tile_meta[1] = found;
+      if (found <= cap) {
+        tile_base[nt] = found;
+        tile_seg[nt] = n_seg;
+      }
+    }
+  }
   if (blockIdx.x == 0) {
-    for (u32 q = threadIdx.x; q <= n_seg; q += AH_BLOCK) seg_off[q] = s_off[q];
     // candidate-list statistics: candidates, their windows, full slices,
     // most of one slice
     const u32 GS = gridDim.x * AH_SPW;
@@ -845,7 +922,8 @@ extern "C" __global__ __launch_bounds__(AH_BLOCK) void ah_emit_seg_kernel(
     const u32 m[4] = {mk.x, mk.y, mk.z, mk.w};
 #if AH_QUAD_ONE_PAIR
     {  // f - 1: the first place the exact count reserved in the segment
-      u64 slot = s_off[ah_pat_pair(e.z) * seg_n + e.x] + (f - 1u);
+      const u32 sg = ah_pat_pair(e.z) * seg_n + e.x;
+      u64 slot = (big ? seg_off[sg] : s_off[sg]) + (f - 1u);
 #pragma unroll
       for (int q = 0; q < 4; ++q)
         if (m[q]) slot += ah_verify_one(c, c.gw + e.y, e.y, e.z + (u32)q, m[q], out, cap, slot, true);
@@ -864,7 +942,7 @@ extern "C" __global__ __launch_bounds__(AH_BLOCK) void ah_emit_seg_kernel(
       }
     if (one) {
       const u32 sg = pq * seg_n + e.x;
-      u64 slot = s_off[sg] + atomicAdd(&seg_fill[sg], f);
+      u64 slot = (big ? seg_off[sg] : s_off[sg]) + atomicAdd(&seg_fill[ah_seg_slot(pq, e.x)], f);
 #pragma unroll
       for (int q = 0; q < 4; ++q)
         if (m[q]) slot += ah_verify_one(c, c.gw + e.y, e.y, e.z + (u32)q, m[q], out, cap, slot, true);
@@ -874,8 +952,9 @@ extern "C" __global__ __launch_bounds__(AH_BLOCK) void ah_emit_seg_kernel(
         if (m[q]) {
           const u32 fq = ah_verify_one(c, c.gw + e.y, e.y, e.z + (u32)q, m[q], nullptr, 0, 0, false);
           if (!fq) continue;
-          const u32 sg = ah_pat_pair(e.z + (u32)q) * seg_n + e.x;
-          const u64 slot = s_off[sg] + atomicAdd(&seg_fill[sg], fq);
+          const u32 pp = ah_pat_pair(e.z + (u32)q), sg = pp * seg_n + e.x;
+          const u64 slot =
+              (big ? seg_off[sg] : s_off[sg]) + atomicAdd(&seg_fill[ah_seg_slot(pp, e.x)], fq);
           ah_verify_one(c, c.gw + e.y, e.y, e.z + (u32)q, m[q], out, cap, slot, true);
         }
     }
