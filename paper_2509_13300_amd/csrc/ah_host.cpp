@@ -900,6 +900,12 @@ bool wave_mode(const std::vector<Pattern>& pats, Tuning tn) {
 // its own runs it at a higher occupancy (64-pair batch: 1.6 ms slower in the
 // filter, against 1.2 ms saved over 64 single-pair tile-mode queries).
 constexpr size_t kTileCountPatterns = 16;
+// Up to this many patterns the exact count is code generated for each, with a
+// switch: its lanes diverge over at most the four of a pair, and the code is
+// the faster then (1.7 M candidates of one pair: 653 us a query against 691 by
+// table).  More read a table (AH_TABLE_COUNT of the scan core): 9.2 M candidates
+// of 256 patterns are counted in 460 us instead of 682, and emitted in 224 instead of 280.
+constexpr size_t kSwitchPatterns = 4;
 
 std::string gen_program_uncached(const std::vector<Pattern>& pats, bool has_n, Tuning tn) {
   int lmax = 0;
@@ -909,6 +915,7 @@ std::string gen_program_uncached(const std::vector<Pattern>& pats, bool has_n, T
   const bool tile_count = !wave && pats.size() <= kTileCountPatterns;
   std::string s;
   char buf[2048];
+  const bool table = pats.size() > kSwitchPatterns;
   // every quad of patterns (4 from the start of each group) within one pair
   bool uniform = true;
   for (size_t a = 0; a < pats.size(); a += (size_t)tn.group)
@@ -917,13 +924,14 @@ std::string gen_program_uncached(const std::vector<Pattern>& pats, bool has_n, T
         uniform &= pats[r].pair == pats[q].pair;
   snprintf(buf, sizeof buf,
            "#define AH_U %d\n#define AH_HALO %d\n#define AH_HAS_N %d\n#define AH_WAVE %d\n"
-           "#define AH_QUAD_ONE_PAIR %d\n#define AH_TILE_COUNT %d\n#define AH_PAIRS %uu\n",
+           "#define AH_QUAD_ONE_PAIR %d\n#define AH_TILE_COUNT %d\n#define AH_PAIRS %uu\n"
+           "#define AH_TABLE_COUNT %d\n",
            tn.u, lmax - 1, has_n ? 1 : 0, wave ? 1 : 0, uniform ? 1 : 0, tile_count ? 1 : 0,
-           pats.empty() ? 1u : pats.back().pair + 1u);
+           pats.empty() ? 1u : pats.back().pair + 1u, table ? 1 : 0);
   std::string head = buf;
   for (size_t i = 0; i < pats.size(); ++i) {
     s += gen_filter(i, pats[i], plan_filter(pats[i], allow));
-    s += gen_exact(i, pats[i], has_n);
+    if (!table) s += gen_exact(i, pats[i], has_n);
   }
   // groups of consecutive patterns; one function per group walks the tile:
   // each lane converts the words of its AH_U window words once and runs
@@ -974,6 +982,21 @@ std::string gen_program_uncached(const std::vector<Pattern>& pats, bool has_n, T
     s += "__device__ void ah_groups(ah_lds_uint2* tw, u32 t0, const AhCtx& c, const AhCands& k) {\n";
     for (size_t gi = 0; gi < ngroups; ++gi) s += "  ah_group_" + std::to_string(gi) + "(tw, t0, c, k);\n";
     s += "}\n";
+  }
+  if (table) {  // sets by position, length and k, clamp, pair, strand and primer
+    s += "__device__ const uint4 ah_pat_tab[] = {\n";
+    for (const Pattern& p : pats) {
+      uint32_t set[4] = {0, 0, 0, 0};
+      for (int j = 0; j < p.L; ++j)
+        for (int q = 0; q < 4; ++q)
+          if (p.mask[j] >> q & 1) set[q] |= 1u << j;
+      snprintf(buf, sizeof buf, "  {%uu, %uu, %uu, %uu}, {%uu, %uu, %uu, %uu},\n", set[0], set[1],
+               set[2], set[3], (uint32_t)p.L | p.k << 8, p.clamp_bits, p.pair,
+               (p.strand << 1) | p.primer);
+      s += buf;
+    }
+    s += "};\n";
+    return head + std::string(kScanCore) + s;
   }
   // verification: the candidate's words from HBM, then the pattern's count
   snprintf(buf, sizeof buf,

@@ -46,7 +46,8 @@
 // positions mismatch every primer position), AH_WAVE (1: wave mode, below),
 // AH_QUAD_ONE_PAIR (1: the four patterns of every candidate record belong to
 // one primer pair), AH_TILE_COUNT (1: in tile mode the filter takes the exact
-// count), AH_PAIRS (primer pairs of the set).
+// count), AH_PAIRS (primer pairs of the set), AH_TABLE_COUNT (1: the exact count
+// reads a table of the patterns instead of running code of its own for each).
 
 typedef unsigned int u32;
 typedef unsigned long long u64;
@@ -262,6 +263,60 @@ typedef __attribute__((address_space(3))) const uint2 ah_lds_uint2;
 // Generated: every group of patterns in turn filters the staged tile and
 // appends its candidates.
 __device__ void ah_groups(ah_lds_uint2* tw, u32 t0, const AhCtx& c, const AhCands& k);
+#if AH_TABLE_COUNT
+// Programs of many patterns: the exact count from a table instead of code for
+// each pattern.  The lanes of a wave hold candidates of different patterns, and
+// a switch over them runs one after the other; here every lane takes its
+// pattern's sets from memory and its windows one at a time (a candidate has
+// one or two): the window's bases as two bit vectors over the positions, then
+// a handful of operations whatever the pattern.
+// Generated, two uint4 a pattern: the positions whose set holds A, C, G, T; length
+// | k << 8, clamp positions, primer pair, strand and primer.
+extern __device__ const uint4 ah_pat_tab[];
+__device__ __forceinline__ u32 ah_pat_pair(u32 p) { return ah_pat_tab[2 * p + 1].z; }
+
+__device__ __forceinline__ u32 ah_verify_one(const AhCtx& c, const uint2* w, u32 t, u32 p, u32 cand,
+                                             AhHitRec* out, u64 cap, u64 slot, bool emit) {
+  const uint4 set = ah_pat_tab[2 * p], meta = ah_pat_tab[2 * p + 1];
+  const u32 L = meta.x & 0xffu, k = meta.x >> 8, all = 0xffffffffu >> (32u - L);
+  u32 hb = cand & ah_valid(c, t, L);
+  if (!hb) return 0u;
+  uint2 v[AH_HALO + 1];
+  __builtin_memcpy(v, w, sizeof v);
+#if AH_HAS_N
+  u32 nm[AH_HALO + 1];
+  __builtin_memcpy(nm, c.gn + t, sizeof nm);
+#endif
+  u32 found = 0;
+  for (; hb; hb &= hb - 1u) {
+    const u32 b = __ffs(hb) - 1u;
+    u32 h = 0, l = 0, n = 0;  // bit j: position j's base, and whether it is one
+#pragma unroll
+    for (int j = 0; j <= AH_HALO; ++j) {
+      h |= ((v[j].x >> b) & 1u) << j;
+      l |= ((v[j].y >> b) & 1u) << j;
+#if AH_HAS_N
+      n |= ((nm[j] >> b) & 1u) << j;
+#endif
+    }
+    const u32 match = (~(h | l) & set.x) | (~h & l & set.y) | (h & ~l & set.z) | (h & l & set.w);
+    const u32 miss = (~match | n) & all, mm = (u32)__popc(miss);
+    if (mm > k || (miss & meta.y) != 0u) continue;
+    if (emit && slot + found < cap) {
+      AhHitRec r;
+      r.genome = c.g;
+      r.pos = b * c.S + t;
+      r.pair = (unsigned short)meta.z;
+      r.strand_primer = (unsigned char)meta.w;
+      r.mm = (unsigned char)mm;
+      r.tm = __int_as_float(0x7fc00000);
+      out[slot + found] = r;
+    }
+    ++found;
+  }
+  return found;
+}
+#else
 // Generated: exact count of the candidate windows `cand` of pattern `p` at
 // window word t, whose words t, t + 1, ... are w[0], w[1], ...; returns the
 // binding sites found and, when `emit`, writes their records from `slot` on.
@@ -270,6 +325,7 @@ __device__ u32 ah_verify_one(const AhCtx& c, W w, u32 t, u32 p, u32 cand, AhHitR
                              u64 slot, bool emit);
 // Generated: the primer pair of pattern p.
 __device__ u32 ah_pat_pair(u32 p);
+#endif
 
 // Where a segment's count and fill counter lie: by genome, then pair, so that the
 // pairs of one genome share a cache line rather than the genomes of one pair
