@@ -303,6 +303,9 @@ Factor match_factor(uint8_t m, int j) {
   return f;
 }
 
+// Literals of a match factor.
+int match_factor_literals(uint8_t m) { return set_size(m) == 2 && !code_planes() ? 2 : 1; }
+
 // One v_bitop3_b32 computing acc? & factors (at most 3 literals in total).
 std::string and_op(const std::string& acc, const std::vector<Factor>& fs) {
   std::vector<Lit> in;
@@ -351,6 +354,21 @@ int and_chain(const std::vector<Factor>& fs, const std::string& dst, std::string
     }
     if (out) *out += "  " + std::string(acc.empty() ? "u32 " : "") + dst + " = " + and_op(acc, take) + ";\n";
     acc = dst;
+    ++ops;
+  }
+  return ops;
+}
+
+// The operations and_chain takes for n1 factors of one literal and n2 of two.
+int chain_ops(int n1, int n2) {
+  int ops = 0;
+  while (n1 > 0 || n2 > 0) {
+    int slots = ops == 0 ? 3 : 2;
+    if (n2 > 0) {
+      --n2;
+      slots -= 2;
+    }
+    n1 -= std::min(slots, n1);
     ++ops;
   }
   return ops;
@@ -441,7 +459,7 @@ int threshold(int B, int need, const std::string& dst, std::string* out) {
 }
 
 // Filter of one pattern.  mode 1 (pigeonhole): the non-clamp, non-N positions
-// are split into k + need blocks; a window with at most k mismatches there
+// (as many of them as pay) are split into k + need blocks; a window with at most k mismatches there
 // leaves at least `need` of them clean.  mode 0 (exact): the bit-sliced
 // mismatch count itself, for patterns whose blocks would pass too many
 // windows.  In both modes the clamp positions must match.
@@ -483,10 +501,10 @@ double cand_weight() {
   return w > 0 ? w : 20.0;
 }
 
-double cand_cost(double rate, int L) {
+double cand_cost(double rate, int L, double weight) {
   const double wave = 1.0 - std::pow(1.0 - std::min(rate, 1.0), 32.0 * 64.0);
   const double per_word = 1.0 - std::pow(1.0 - std::min(rate, 1.0), 32.0);
-  return 14.0 * wave + cand_weight() * per_word * 8.0 * L;
+  return 14.0 * wave + weight * per_word * 8.0 * L;
 }
 
 // Development knob (AH_SCAN_FORCE_NEED = 1, 2 or 3): plan only pigeonhole
@@ -498,7 +516,15 @@ int forced_need() {
   return n >= 1 && n <= 3 ? n : 0;
 }
 
-FilterPlan plan_filter_uncached(const Pattern& p, bool allow) {
+// Highest pass rate of a filter that leaves positions of its primer out.  A
+// specific primer at few mismatches needs only part of its positions for a rate
+// at which candidates cost nothing (27 positions at k = 0 pass one window in
+// 10^16; 10 of them one in 10^6): 64 pairs at k = 0-3 on 500 genomes take 8.17 ms a
+// query with every position tested, 7.49 at 1e-7, 7.33 at 5e-7, 7.22 at 2e-6; one
+// pair at k = 0 on 1,000 genomes 0.29 and 0.26.
+constexpr double kLeaveOutRate = 5e-7;
+
+FilterPlan plan_filter_uncached(const Pattern& p, bool allow, double weight) {
   std::vector<int> free_pos;
   std::vector<Factor> clampf;
   double clamp_p = 1.0;
@@ -523,7 +549,7 @@ FilterPlan plan_filter_uncached(const Pattern& p, bool allow) {
   FilterPlan best;
   best.mode = 0;
   best.rate = exact_rate;
-  best.cost = exact_ops + clamp_ops + 2 + cand_cost(exact_rate, p.L);
+  best.cost = exact_ops + clamp_ops + 2 + cand_cost(exact_rate, p.L, weight);
   if (!allow) return best;
   const int force = forced_need();
   if (force) best.cost = 1e300;  // any pigeonhole plan with that need wins
@@ -551,53 +577,104 @@ FilterPlan plan_filter_uncached(const Pattern& p, bool allow) {
     // cost of a partition: chain operations (a 3-input chain over I inputs
     // takes ceil((I - 1) / 2), so odd input counts waste no slot), the
     // threshold, the clamp, and the candidates it lets through
+    const int threshold_ops = threshold(B, need, "r", nullptr);
+    std::vector<double> clean(B);
     auto evaluate = [&](const std::vector<std::vector<int>>& bl, double* rate_out) {
-      std::vector<double> clean(B);
-      int ops = 0;
+      int ops = threshold_ops;
       for (int b = 0; b < B; ++b) {
         double bb = 0.0;
-        std::vector<Factor> fs;
+        int n1 = 0, n2 = 0;
         for (int j : bl[b]) {
-          fs.push_back(match_factor(p.mask[j], j));
+          (match_factor_literals(p.mask[j]) == 1 ? n1 : n2)++;
           bb += std::log2(4.0 / set_size(p.mask[j]));
         }
         clean[b] = std::exp2(-bb);
-        ops += and_chain(fs, "k", nullptr);
+        ops += chain_ops(n1, n2);
       }
-      ops += threshold(B, need, "r", nullptr);
       const double rate = clamp_p * at_least(clean, need);
       if (rate_out) *rate_out = rate;
-      return ops + clamp_ops + 1 + cand_cost(rate, p.L);
+      return ops + clamp_ops + 1 + cand_cost(rate, p.L, weight);
     };
     double rate = 1.0;
     double cost = evaluate(blocks, &rate);
+    // positions with sets of one size cost the same: the first of each size in
+    // a block stands for them (`skip` of them passed over)
+    auto first_of = [&](const std::vector<int>& bl, int size, int skip) {
+      for (size_t q = 0; q < bl.size(); ++q)
+        if (set_size(p.mask[bl[q]]) == size && skip-- == 0) return (int)q;
+      return -1;
+    };
     // local search: move one position to another block while that lowers
     // the cost (typically evening out input counts to odd ones)
-    for (int iter = 0; iter < 64; ++iter) {
-      double best_move = cost;
-      int ba = -1, bb = -1, ja = -1;
-      for (int a = 0; a < B; ++a) {
-        if (blocks[a].size() < 2) continue;
-        for (size_t q = 0; q < blocks[a].size(); ++q)
-          for (int b = 0; b < B; ++b) {
-            if (b == a) continue;
-            auto trial = blocks;
-            trial[b].push_back(trial[a][q]);
-            trial[a].erase(trial[a].begin() + (long)q);
-            const double c2 = evaluate(trial, nullptr);
-            if (c2 < best_move - 1e-9) {
-              best_move = c2;
-              ba = a;
-              bb = b;
-              ja = (int)q;
+    auto search_moves = [&] {
+      for (int iter = 0; iter < 64; ++iter) {
+        double best_move = cost;
+        int ba = -1, bb = -1, ja = -1;
+        for (int a = 0; a < B; ++a) {
+          if (blocks[a].size() < 2) continue;
+          for (size_t q = 0; q < blocks[a].size(); ++q) {
+            if (first_of(blocks[a], set_size(p.mask[blocks[a][q]]), 0) != (int)q) continue;
+            for (int b = 0; b < B; ++b) {
+              if (b == a) continue;
+              auto trial = blocks;
+              trial[b].push_back(trial[a][q]);
+              trial[a].erase(trial[a].begin() + (long)q);
+              const double c2 = evaluate(trial, nullptr);
+              if (c2 < best_move - 1e-9) {
+                best_move = c2;
+                ba = a;
+                bb = b;
+                ja = (int)q;
+              }
             }
           }
+        }
+        if (ba < 0) break;
+        blocks[bb].push_back(blocks[ba][ja]);
+        blocks[ba].erase(blocks[ba].begin() + ja);
+        cost = evaluate(blocks, &rate);
       }
-      if (ba < 0) break;
-      blocks[bb].push_back(blocks[ba][ja]);
-      blocks[ba].erase(blocks[ba].begin() + ja);
-      cost = evaluate(blocks, &rate);
-    }
+    };
+    // Positions left out of the filter (the exact count tests them all): one or two of a
+    // block at a time, while that lowers the cost and the pass rate stays
+    // below kLeaveOutRate.  A window with at most k mismatches has no more of
+    // them on fewer positions, so it still leaves `need` blocks clean.
+    auto leave_out = [&] {
+      bool any = false;
+      for (;;) {
+        double best_cut = cost;
+        std::vector<int> keep;
+        int at = -1;
+        for (int a = 0; a < B; ++a) {
+          const std::vector<int> whole = blocks[a];
+          const int n = (int)whole.size();
+          for (int z1 = 1; z1 <= 3; ++z1)
+            for (int z2 = 0; z2 <= z1; ++z2) {  // sizes of one position (z2 0) or two
+              const int q1 = first_of(whole, z1, 0);
+              const int q2 = z2 ? first_of(whole, z2, z1 == z2 ? 1 : 0) : q1;
+              if (q1 < 0 || q2 < 0 || n - (z2 ? 2 : 1) < 1) continue;
+              std::vector<int> left;
+              for (int q = 0; q < n; ++q)
+                if (q != q1 && q != q2) left.push_back(whole[q]);
+              blocks[a] = left;
+              double r2 = 1.0;
+              const double c2 = evaluate(blocks, &r2);
+              if (r2 <= kLeaveOutRate && c2 < best_cut - 1e-9) {
+                best_cut = c2;
+                keep = left;
+                at = a;
+              }
+            }
+          blocks[a] = whole;
+        }
+        if (at < 0) return any;
+        blocks[at] = keep;
+        cost = evaluate(blocks, &rate);
+        any = true;
+      }
+    };
+    search_moves();
+    while (leave_out()) search_moves();
     if (cost < best.cost) {
       best.mode = 1;
       best.need = need;
@@ -615,12 +692,12 @@ FilterPlan plan_filter_uncached(const Pattern& p, bool allow) {
 // of 8 one-pair jobs, whose parts are sized under the server's lock, took
 // 24.6 ms with the search repeated and takes 0.9 ms with it kept.  Bounded: a
 // full map is dropped and fills again.
-FilterPlan plan_filter(const Pattern& p, bool allow) {
+FilterPlan plan_filter(const Pattern& p, bool allow, double weight) {
   static std::mutex mu;
   static std::map<std::string, FilterPlan> cache;
   char buf[96];
   const int n = snprintf(buf, sizeof buf, "%d|%d|%u|%x|%d|%.17g|%d|", allow ? 1 : 0, p.L, p.k,
-                         p.clamp_bits, code_planes() ? 1 : 0, cand_weight(), forced_need());
+                         p.clamp_bits, code_planes() ? 1 : 0, weight, forced_need());
   std::string key(buf, (size_t)n);
   key.append((const char*)p.mask, (size_t)p.L);
   {
@@ -628,7 +705,7 @@ FilterPlan plan_filter(const Pattern& p, bool allow) {
     auto it = cache.find(key);
     if (it != cache.end()) return it->second;
   }
-  FilterPlan plan = plan_filter_uncached(p, allow);
+  FilterPlan plan = plan_filter_uncached(p, allow, weight);
   std::lock_guard<std::mutex> lk(mu);
   if (cache.size() >= 8192) cache.clear();
   cache.emplace(std::move(key), plan);
@@ -907,6 +984,14 @@ constexpr size_t kTileCountPatterns = 16;
 // of 256 patterns are counted in 460 us instead of 682, and emitted in 224 instead of 280.
 constexpr size_t kSwitchPatterns = 4;
 
+// A candidate's weight in the planning of a program's filters.  Programs of many
+// patterns pay double: a group of 16 takes the append branch for any of them, in
+// lanes of different patterns (64 pairs on 500 genomes: 7.33 ms a query at 20,
+// 7.11 at 40; one pair with 1.7 M candidates: 0.65 at 20, 0.71 at 30 and above).
+double program_weight(const std::vector<Pattern>& pats) {
+  return cand_weight() * (pats.size() > kTileCountPatterns ? 2.0 : 1.0);
+}
+
 std::string gen_program_uncached(const std::vector<Pattern>& pats, bool has_n, Tuning tn) {
   int lmax = 0;
   for (const Pattern& p : pats) lmax = p.L > lmax ? p.L : lmax;
@@ -930,7 +1015,7 @@ std::string gen_program_uncached(const std::vector<Pattern>& pats, bool has_n, T
            pats.empty() ? 1u : pats.back().pair + 1u, table ? 1 : 0);
   std::string head = buf;
   for (size_t i = 0; i < pats.size(); ++i) {
-    s += gen_filter(i, pats[i], plan_filter(pats[i], allow));
+    s += gen_filter(i, pats[i], plan_filter(pats[i], allow, program_weight(pats)));
     if (!table) s += gen_exact(i, pats[i], has_n);
   }
   // groups of consecutive patterns; one function per group walks the tile:
@@ -1445,9 +1530,10 @@ uint64_t min_cands(uint64_t cap) { return std::max<uint64_t>(cap, 1ull << 16); }
 // (uniform bases).
 double cand_per_word(const std::vector<Pattern>& pats) {
   const bool allow = filter_enabled();
+  const double weight = program_weight(pats);
   double r = 0.0;
   for (const Pattern& p : pats) {
-    const double rate = std::min(plan_filter(p, allow).rate, 1.0);
+    const double rate = std::min(plan_filter(p, allow, weight).rate, 1.0);
     r += 1.0 - std::pow(1.0 - rate, 32.0);
   }
   return r;
