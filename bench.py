@@ -1051,7 +1051,7 @@ def main():
                       "captured once; the same K steps launched call by call under 'eager'",
             "eager": {"ms_per_step": r["ms_per_step"], "gbps": r["value"]},
             "ingest_pack": r["pack"], "jit": r["jit"],
-            "tm_dtype": "f32 (compensated sums, f64 salt/log terms)",
+            "tm_dtype": "f32 (exact fixed-point stack sums, f64 salt/log terms)",
             "oracle_equal": None if agree is None else agree["oracle_equal"],
             "tm_error": None if agree is None else agree["tm_error"],
             "oracle_check": None if agree is None else {

@@ -344,7 +344,7 @@ size_t ah_pair_workspace_bytes(uint64_t hit_capacity, uint32_t n_pairs);
  * genome) that fit beside the workspace's sort buffers, the scan puts the sites
  * of each segment together, and one launch takes them in tiles of whole
  * segments, a workgroup each: it sorts them into canonical order (in LDS up to
- * 1,024 sites, or 4,096 where hit_capacity is above 131,072), computes their
+ * 1,024 sites, or 4,096 where many are expected), computes their
  * Tm, counts the amplicons each + site starts, takes its first amplicon slot
  * from the counts of the earlier tiles and writes its amplicons.  With more
  * segments, when a pair is expected to give more than 512 sites on the longest

@@ -1624,7 +1624,7 @@ ah_status check_genomes(const ah_genomes* g) {
 // Segment buffers of ah_query, carved from the workspace's radix-sort
 // buffers, which its segmented tail does not use.  False when the segments
 // are more than kSegMax, their sort keys too wide, or the buffers do not fit.
-bool carve_seg(const ScanWs& w, uint32_t n_genomes, uint64_t n_seg, uint64_t cap,
+bool carve_seg(const ScanWs& w, uint32_t n_genomes, uint64_t n_seg, uint64_t cap, double expected,
                const ah::KeyBits& kb, ah::SegBuffers& sg) {
   if (n_seg == 0 || n_seg > ah::kSegMax) return false;
   // a tile's keys: its segments, pos << 2 | strand-primer, 12 bits of index
@@ -1633,12 +1633,13 @@ bool carve_seg(const ScanWs& w, uint32_t n_genomes, uint64_t n_seg, uint64_t cap
   const uintptr_t end = (uintptr_t)w.sb.hist[2] +
                         (uintptr_t)ah::kSortDigits * w.sb.hstride * sizeof(uint32_t);
   Carver c((void*)beg, (size_t)(end - beg));
-  // Small capacities: workgroups of one wave, whose tiles of a few dozen sites
-  // pass through with no barrier (16 references 34.2 us a query against 36.1,
-  // 20,000 contigs with 18,000 sites 144 against 156 us).  Beyond 2^17 sites, tiles of
-  // hundreds (430,000 sites of a 64-pair panel 8.45 ms against 8.57).
-  sg.wide = cap > 131072;
-  sg.t_n = sg.wide ? 512 : 128;
+  // Workgroups of one wave pass tiles of a few dozen sites through with no
+  // barrier (16 references 34.2 us a query against 36.1, 20,000 contigs with
+  // 18,000 sites 144 against 156).  Where tens of thousands of random sites are
+  // expected and there is room for more than 2^17, tiles of hundreds (430,000 sites of a
+  // 64-pair panel 8.45 ms against 8.57).
+  sg.wide = cap > 131072 && expected > 32768.0;
+  sg.t_n = cap > 131072 ? 512 : 128;
   sg.t_seg = sg.wide ? 1024 : 128;
   sg.n_tiles = (uint32_t)std::min<uint64_t>(std::max<uint64_t>(1024, (cap + sg.t_n - 1) / sg.t_n),
                                             cap / 32 + 1);
@@ -1663,16 +1664,20 @@ bool carve_seg(const ScanWs& w, uint32_t n_genomes, uint64_t n_seg, uint64_t cap
 // strands) decide, against kSegExpected; AH_QUERY_SEGMENTED=1 or 0 forces one
 // tail (the segmented one still only up to kSegMax segments).
 constexpr double kSegExpected = 512.0;
-bool seg_mode(const ah_primer_pair* pairs, uint32_t n_pairs, uint32_t max_len) {
+// *expected: the random sites of all pairs on n genomes of that length.
+bool seg_mode(const ah_primer_pair* pairs, uint32_t n_pairs, uint32_t n, uint32_t max_len,
+              double* expected) {
   const char* e = getenv("AH_QUERY_SEGMENTED");
   if (e && e[0] == '0') return false;
-  if (e && e[0] == '1') return true;
+  double most = 0.0, sum = 0.0;
   for (uint32_t q = 0; q < n_pairs; ++q) {
     const double rate = 2.0 * (ah::site_probability(pairs[q].fwd, pairs[q].k, pairs[q].clamp) +
                                ah::site_probability(pairs[q].rev, pairs[q].k, pairs[q].clamp));
-    if (rate * (double)max_len > kSegExpected) return false;
+    most = std::max(most, rate * (double)max_len);
+    sum += rate * (double)max_len * (double)n;
   }
-  return true;
+  *expected = sum;
+  return (e && e[0] == '1') || most <= kSegExpected;
 }
 
 // Reset of d_res, tile counts and prefix, then the filter, the exact count
@@ -2421,8 +2426,9 @@ ah_status ah_query(const ah_genomes* g, const ah_primer_pair* pairs, const ah_wi
   const auto* ttab = (const ah::PrimerTab*)tm_tabs;
   const auto* ptab = (const ah::PairTab*)pair_tabs;
   ah::SegBuffers sg{};
-  if (g->n > 0 && seg_mode(pairs, n_pairs, g->max_len) &&
-      carve_seg(w, g->n, (uint64_t)n_pairs * g->n, hit_capacity, kb, sg)) {
+  double expected = 0.0;
+  if (g->n > 0 && seg_mode(pairs, n_pairs, g->n, g->max_len, &expected) &&
+      carve_seg(w, g->n, (uint64_t)n_pairs * g->n, hit_capacity, expected, kb, sg)) {
     // each segment (pair, genome) sorted, its Tm and amplicons, by one workgroup
     s = launch_scan_kernel(fn, tn, g, w, d_hit_res, hit_capacity, st, nullptr, &sg);
     if (s) return s;

@@ -1,8 +1,9 @@
 """The tiles of ah_query's segmented tail, byte for byte against the three
 separate calls: many short segments (thousands of genomes, most of them without a
 site), segments that fill tiles by themselves, segments longer than a tile's LDS in
-either form (one wave up to a capacity of 2^17 sites, four beyond), no site at all,
-and overflows."""
+either form (four waves where the capacity is above 2^17 sites and more than 32,768
+are expected on genomes of the longest's length, else one), no site at all, and
+overflows."""
 import numpy as np
 import pytest
 
@@ -21,14 +22,15 @@ SHORT = plan.PairSpec("ACGTACGTAC", "GGCCAATTGG", k=3, clamp=0, min_len=20, max_
 def test_many_short_segments(dev, n, pairs, cap):  # noqa: F811
     p = plan.tiny(9400 + n, n_genomes=n, len_lo=30, len_hi=900, n_copies=(0, 1), span=100,
                   pair=plan.PairSpec("ACGTRYACGTAC", "TTGCANNGCATT", k=2, clamp=0, min_len=20, max_len=400))
-    ps = [p.pairs[0]] + plan.law_pairs(9401, pairs - 1)
+    ps = [p.pairs[0]] + plan.law_pairs(9401, pairs - 1) + ([SHORT] if cap == WIDE else [])
     sep, fus = _both(p, ps, dev, hit_cap=cap, amp_cap=1 << 16, filter_tm=pairs == 3, min_tm=25.0)
     say("short segments", n, pairs, cap, sep[0]["count"], sep[1]["count"])
     assert sep[0]["status"] == 0 and sep[0]["count"] > 500 and fus == sep
 
 
 @pytest.mark.parametrize("cap", [NARROW, WIDE])
-@pytest.mark.parametrize("lengths", [[3000] * 200, [90_000, 10, 120_000, 31, 31, 60_000], [700_000, 20, 5000]])
+@pytest.mark.parametrize("lengths", [[3000] * 200 + [60_000], [90_000, 120_000, 31, 60_000] + [10] * 40,
+                                     [700_000, 5000] + [20] * 10])
 def test_long_segments(dev, monkeypatch, lengths, cap):  # noqa: F811
     """From a few sites a segment to more than 4,096 (forced: left to itself the
     query expects segments this long and takes the radix tail)."""
