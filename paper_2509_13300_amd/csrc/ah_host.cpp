@@ -1958,7 +1958,8 @@ bool tm_exact_forced() {
 }
 
 // Whether the route applies: a Tm that depends on the pairing alone and a
-// negative denominator for every pairing.
+// negative denominator for every pairing.  The kernels' test that no pairing is
+// above the representative's rests on the same (PrimerTab::neg).
 bool tm_exact_applies(const ah_tm_params& p, const SaltTerms& salt_t, int L) {
   return !salt_t.recip && tm_denominator_const(p, salt_t, L) + kMaxPairingDs < 0.0;
 }
@@ -2050,6 +2051,7 @@ ah_status tm_table(const PairSet& ps, uint32_t n_pairs, const ah_tm_params& pp, 
       for (uint32_t j = 0; j < ps.clamp[q]; ++j) t.clampm |= 1ull << (2 * (pr.L - 1 - (int)j));
       t.decoy = (ps.flags[q] & AH_PAIR_DECOY) ? 1u : 0u;
       t.KL = tm_denominator_const(*p, salt_t, pr.L);
+      t.neg = tm_exact_applies(*p, salt_t, pr.L) ? 1u : 0u;
       t.dp = tm_exact_route(pr, ps.k[q], ps.clamp[q], *p, salt_t) ? 1u : 0u;
       any_exact |= t.dp != 0u;
       t.tshift = salt_t.shift;

@@ -40,7 +40,8 @@ struct PrimerTab {
   uint32_t L, k;
   uint32_t decoy;     // 1: the site is the primer against the reversed genome
   uint32_t dp;        // 1: exact best pairing (ratio iteration), not enumeration
-  uint32_t reserved;
+  uint32_t neg;       // 1: Tm depends on the pairing alone (no recip) and Delta-S + KL
+                      // is negative for every pairing
 };
 
 // Per-pair table used by the pairing kernels.

@@ -885,14 +885,17 @@ __device__ __forceinline__ float tm_pairing(const TmRep& r, const PrimerTab* T, 
 // (tm, no reciprocal correction).  With T that Tm in kelvin, unpairing
 // positions adds g = 1000 |Delta-H| - T |Delta-S| of every stack it breaks, and
 // of changes at the two outermost pairs, to 1000 Delta-H - T (Delta-S + KL), and
-// lowers the Tm when that sum is positive.  So it is enough that the outermost
-// pairs cannot be unpaired and that every stack next to a position that can be
-// has g > 1 (a loss above 1e-3 degrees, past every rounding).
+// lowers the Tm when that sum is positive and the other pairing's denominator
+// Delta-S + KL is negative.  So it is enough that the denominator is negative for
+// every pairing of the primer (T->neg: breaking stacks raises it, and a pairing
+// that lifts it above zero can have any Tm), that the outermost pairs cannot be
+// unpaired, and that every stack next to a position that can be has g > 1 (a loss
+// above 1e-3 degrees, past every rounding).
 __device__ __forceinline__ bool tm_rep_is_best(const TmRep& r, const PrimerTab* T, float tm,
                                                const NnFix* s_nn) {
-  if (T->recip || r.eq0 == 0) return false;
+  if (T->neg == 0u || r.eq0 == 0) return false;
   const u64 lo = r.eq0 & (0ull - r.eq0), hi = 1ull << (63u - (u32)__clzll((long long)r.eq0));
-  if ((r.afree & (lo | hi)) != 0ull || !(fix_s(r.s0) + T->KL < -20.0)) return false;
+  if ((r.afree & (lo | hi)) != 0ull) return false;
   const float t = tm + 273.15f;
   for (u64 st = r.st0 & (r.afree | (r.afree >> 2)); st; st &= st - 1) {
     const NnFix v = s_nn[(u32)(r.o >> ((u32)__ffsll((long long)st) - 1u)) & 15u];
