@@ -26,6 +26,13 @@ DEVFLAGS = ["-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
 COMMON = ["-O3", "-std=c++17", "-fPIC", f"--offload-arch={ARCH}", f"-I{INCLUDE}", f"-I{CSRC}",
           f"-I{BUILD}"]
 
+# The FASTA reader's loops over bytes, a handful of instructions each, start on
+# cache lines of their own: where the linker put them otherwise moved with the
+# size of the other objects.  Counting the records of a 31 MB text, best of 15
+# runs on 8 threads of a 2.7 GHz Xeon, took 3.5-4.4 ms by where they fell and takes
+# 3.4-3.5 aligned; on an EPYC host 1.59 ms (median) fell to 1.52.
+EXTRA = {"ah_fasta_io.cpp": ["-falign-functions=64", "-falign-loops=64"]}
+
 # Run-time specialisations compiled once at build time (through the built
 # library's own generator and hipRTC) so that a mistake in the scan core or
 # the generator fails the build rather than the first call: degenerate sets,
@@ -70,7 +77,7 @@ def build(verbose: bool = False) -> str:
         src = os.path.join(CSRC, name)
         obj = os.path.join(BUILD, name + ".o")
         lang = ["-x", "hip"] if name.endswith(".hip") else []
-        _run([HIPCC, *COMMON, *DEVFLAGS, *lang, "-c", src, "-o", obj])
+        _run([HIPCC, *COMMON, *DEVFLAGS, *EXTRA.get(name, []), *lang, "-c", src, "-o", obj])
         objs.append(obj)
     # the compile helper: scan programs compile in processes of their own
     helper = os.path.join(HERE, "ah_jitc")
