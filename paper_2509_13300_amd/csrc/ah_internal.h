@@ -147,6 +147,9 @@ hipError_t launch_sort_tm_mark(ah_hit* staged, ah_hit* out, const uint64_t* n_de
 // out in canonical order with their Tm when they fit in hcap (a full
 // candidate list), as the separate calls write them.
 constexpr uint32_t kSegMax = 1u << 17;
+// Tiles at most: as many as cost a query with few sites next to nothing (each
+// idle one is a workgroup that starts and ends), times t_n sites before T grows.
+constexpr uint32_t kTilesNarrow = 16384, kTilesWide = 4096;
 constexpr uint32_t kSegEmitMax = 4096;  // AH_SEG_MAX of the scan core: beyond, seg_prefix
 struct SegBuffers {
   uint32_t* cnt;   // [n_seg] sites per segment, then
@@ -158,6 +161,7 @@ struct SegBuffers {
   uint32_t* tile_seg;   // [n_tiles + 1] first segment of each tile
   uint64_t* tile_meta;  // [2] tiles, sites
   uint32_t t_n, t_seg;  // bounds of the sites per tile (from the count, from the mean segment)
+                        // while n_tiles of them hold the count
   uint32_t n_tiles;     // tiles at most, whatever the count
   uint32_t n_zero;         // uint32 words to clear, from cnt on
   bool wide;               // workgroups of 256 threads (else of one wave)

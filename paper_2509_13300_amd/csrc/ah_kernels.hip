@@ -290,8 +290,10 @@ __device__ __forceinline__ u64 run_prefix(u32 n, const ValF& val, const PutF& pu
 
 // Tile counts of n <= kSmallPrefix genomes and their exclusive prefix (n + 1
 // entries), the result reset, and the clearing of `zero` and `zero64` (every
-// workgroup a part).  20,000 genomes: 11 us (29 us by one workgroup, 20 values a
-// thread; six launches and 20 us as a scan in three with the clearing apart).
+// workgroup a part; those past the genomes' runs only clear: the words of a
+// query's segments and tiles may be many more than its genomes).  20,000
+// genomes: 11 us (29 us by one workgroup, 20 values a thread; six launches and
+// 20 us as a scan in three with the clearing apart).
 __global__ __launch_bounds__(kSmallBlock) void k_tile_prefix_small(const u32* __restrict__ len, u32 n,
                                                                    u32 tile_words,
                                                                    u64* __restrict__ prefix,
@@ -300,10 +302,12 @@ __global__ __launch_bounds__(kSmallBlock) void k_tile_prefix_small(const u32* __
                                                                    u32 n_zero64) {
   for (u32 i = (u32)global_tid(); i < n_zero; i += (u32)grid_threads()) zero[i] = 0u;
   for (u32 i = (u32)global_tid(); i < n_zero64; i += (u32)grid_threads()) zero64[i] = 0ull;
+  const u32 runs = (n + kRun - 1) / kRun;
+  if (blockIdx.x >= runs) return;
   const u64 upto = run_prefix(
       n, [&](u32 g) { return (u32)((((u64)len[g] + 31) / 32 + tile_words - 1) / tile_words); },
       [&](u32 g, u64 at) { prefix[g] = at; });
-  if (threadIdx.x == 0 && blockIdx.x + 1 == gridDim.x) {
+  if (threadIdx.x == 0 && blockIdx.x + 1 == runs) {
     prefix[n] = upto;
     r->count = 0;
     r->required = 0;
@@ -2572,9 +2576,10 @@ hipError_t launch_tile_prefix_small(const uint32_t* len, uint32_t n, uint32_t ti
                                     uint64_t* prefix, ah_result* res, hipStream_t st,
                                     uint32_t* zero, uint32_t n_zero, uint64_t* zero64,
                                     uint32_t n_zero64) {
-  k_tile_prefix_small<<<(n + kRun - 1) / kRun, kSmallBlock, 0, st>>>(
-      len, n, tile_words, (u64*)prefix, res, zero, zero ? n_zero : 0u, (u64*)zero64,
-      zero64 ? n_zero64 : 0u);
+  if (!zero) n_zero = 0;
+  if (!zero64) n_zero64 = 0;
+  k_tile_prefix_small<<<(std::max(n, n_zero) + kRun - 1) / kRun, kSmallBlock, 0, st>>>(
+      len, n, tile_words, (u64*)prefix, res, zero, n_zero, (u64*)zero64, n_zero64);
   return hipGetLastError();
 }
 
