@@ -469,6 +469,7 @@ struct FilterPlan {
   std::vector<std::vector<int>> blocks;
   double rate = 1.0;  // chance a random window passes (uniform bases)
   double cost = 0.0;  // estimated lane operations per window word
+  bool left_out = false;  // some position of the primer is not tested
 };
 
 // P(at least `need` of the independent events with probabilities p occur)
@@ -521,7 +522,9 @@ int forced_need() {
 // at which candidates cost nothing (27 positions at k = 0 pass one window in
 // 10^16; 10 of them one in 10^6): 64 pairs at k = 0-3 on 500 genomes take 8.17 ms a
 // query with every position tested, 7.49 at 1e-7, 7.33 at 5e-7, 7.22 at 2e-6; one
-// pair at k = 0 on 1,000 genomes 0.29 and 0.26.
+// pair at k = 0 on 1,000 genomes 0.29 and 0.26.  The rate is that of uniform bases:
+// sequence that repeats the positions kept passes more, and the scan core fills a
+// slice which that overfills again with sites' records (AH_REFILL).
 constexpr double kLeaveOutRate = 5e-7;
 
 FilterPlan plan_filter_uncached(const Pattern& p, bool allow, double weight) {
@@ -681,6 +684,9 @@ FilterPlan plan_filter_uncached(const Pattern& p, bool allow, double weight) {
       best.blocks = blocks;
       best.rate = rate;
       best.cost = cost;
+      size_t tested = 0;
+      for (const auto& bl : blocks) tested += bl.size();
+      best.left_out = tested < free_pos.size();
     }
   }
   return best;
@@ -1001,6 +1007,14 @@ std::string gen_program_uncached(const std::vector<Pattern>& pats, bool has_n, T
   std::string s;
   char buf[2048];
   const bool table = pats.size() > kSwitchPatterns;
+  std::vector<FilterPlan> plans;
+  // The list's sizes are those of uniform bases; where the filters are not the
+  // strongest at the usual weight, a slice that other sequence fills is filled again.
+  bool refill = pats.size() > kTileCountPatterns;
+  for (const Pattern& p : pats) {
+    plans.push_back(plan_filter(p, allow, program_weight(pats)));
+    refill |= plans.back().left_out;
+  }
   // every quad of patterns (4 from the start of each group) within one pair
   bool uniform = true;
   for (size_t a = 0; a < pats.size(); a += (size_t)tn.group)
@@ -1010,12 +1024,14 @@ std::string gen_program_uncached(const std::vector<Pattern>& pats, bool has_n, T
   snprintf(buf, sizeof buf,
            "#define AH_U %d\n#define AH_HALO %d\n#define AH_HAS_N %d\n#define AH_WAVE %d\n"
            "#define AH_QUAD_ONE_PAIR %d\n#define AH_TILE_COUNT %d\n#define AH_PAIRS %uu\n"
-           "#define AH_TABLE_COUNT %d\n",
+           "#define AH_TABLE_COUNT %d\n#define AH_REFILL %d\n"
+           "#define AH_GROUP %du\n#define AH_PATTERNS %zuu\n",
            tn.u, lmax - 1, has_n ? 1 : 0, wave ? 1 : 0, uniform ? 1 : 0, tile_count ? 1 : 0,
-           pats.empty() ? 1u : pats.back().pair + 1u, table ? 1 : 0);
+           pats.empty() ? 1u : pats.back().pair + 1u, table ? 1 : 0, refill ? 1 : 0, tn.group,
+           pats.size());
   std::string head = buf;
   for (size_t i = 0; i < pats.size(); ++i) {
-    s += gen_filter(i, pats[i], plan_filter(pats[i], allow, program_weight(pats)));
+    s += gen_filter(i, pats[i], plans[i]);
     if (!table) s += gen_exact(i, pats[i], has_n);
   }
   // groups of consecutive patterns; one function per group walks the tile:
@@ -1068,7 +1084,7 @@ std::string gen_program_uncached(const std::vector<Pattern>& pats, bool has_n, T
     for (size_t gi = 0; gi < ngroups; ++gi) s += "  ah_group_" + std::to_string(gi) + "(tw, t0, c, k);\n";
     s += "}\n";
   }
-  if (table) {  // sets by position, length and k, clamp, pair, strand and primer
+  if (table || refill) {  // sets by position, length and k, clamp, pair, strand and primer
     s += "__device__ const uint4 ah_pat_tab[] = {\n";
     for (const Pattern& p : pats) {
       uint32_t set[4] = {0, 0, 0, 0};
@@ -1081,8 +1097,8 @@ std::string gen_program_uncached(const std::vector<Pattern>& pats, bool has_n, T
       s += buf;
     }
     s += "};\n";
-    return head + std::string(kScanCore) + s;
   }
+  if (table) return head + std::string(kScanCore) + s;
   // verification: the candidate's words from HBM, then the pattern's count
   snprintf(buf, sizeof buf,
            "template <class W>\n"

@@ -47,7 +47,10 @@
 // AH_QUAD_ONE_PAIR (1: the four patterns of every candidate record belong to
 // one primer pair), AH_TILE_COUNT (1: in tile mode the filter takes the exact
 // count), AH_PAIRS (primer pairs of the set), AH_TABLE_COUNT (1: the exact count
-// reads a table of the patterns instead of running code of its own for each).
+// reads a table of the patterns instead of running code of its own for each),
+// AH_REFILL (1: a full slice is filled again with sites' records, below: programs
+// of which a filter leaves positions of its primer out, and large ones), AH_GROUP and
+// AH_PATTERNS (patterns a group, and in all).
 
 typedef unsigned int u32;
 typedef unsigned long long u64;
@@ -263,6 +266,11 @@ typedef __attribute__((address_space(3))) const uint2 ah_lds_uint2;
 // Generated: every group of patterns in turn filters the staged tile and
 // appends its candidates.
 __device__ void ah_groups(ah_lds_uint2* tw, u32 t0, const AhCtx& c, const AhCands& k);
+#if AH_TABLE_COUNT || AH_REFILL
+// Generated, two uint4 a pattern: the positions whose set holds A, C, G, T; length
+// | k << 8, clamp positions, primer pair, strand and primer.
+extern __device__ const uint4 ah_pat_tab[];
+#endif
 #if AH_TABLE_COUNT
 // Programs of many patterns: the exact count from a table instead of code for
 // each pattern.  The lanes of a wave hold candidates of different patterns, and
@@ -270,9 +278,6 @@ __device__ void ah_groups(ah_lds_uint2* tw, u32 t0, const AhCtx& c, const AhCand
 // pattern's sets from memory and its windows one at a time (a candidate has
 // one or two): the window's bases as two bit vectors over the positions, then
 // a handful of operations whatever the pattern.
-// Generated, two uint4 a pattern: the positions whose set holds A, C, G, T; length
-// | k << 8, clamp positions, primer pair, strand and primer.
-extern __device__ const uint4 ah_pat_tab[];
 __device__ __forceinline__ u32 ah_pat_pair(u32 p) { return ah_pat_tab[2 * p + 1].z; }
 
 __device__ __forceinline__ u32 ah_verify_one(const AhCtx& c, const uint2* w, u32 t, u32 p, u32 cand,
@@ -496,6 +501,222 @@ __device__ __forceinline__ u64 ah_wtile(u64 r, u32 b, u32 wv) {
   return r * V + (u64)b * 4u + wv;
 }
 
+#endif
+
+#if AH_REFILL
+// ---- full slices of programs whose filters leave positions out (and of those with
+// more than 16 patterns, whose filters are chosen by another weight).  Such a filter
+// passes more windows than one that tests every position, on sequence that
+// repeats the positions it kept above all (half the windows of an (AC)n repeat for
+// an AC-rich primer), and could fill a slice where few sites are.  So a slice found
+// full after the last tile is filled again: the records of the tile at which it
+// filled leave it, and of the others those without a site; then that tile's words
+// and those of the later tiles are tested exactly, and records of sites alone are
+// added.  Only a slice that sites' records overfill stays full, and such a query
+// overflows with every filter.  All of it comes after the loop over the tiles: taken
+// inside, tile by tile and only for the words that found no place, it cost every
+// program 5-15 registers, and those near 128 a wave per SIMD (one pair at k = 0-1
+// on 300 genomes: 115 us a query, 124).
+
+// Windows of word t of genome c that are sites of pattern p: a bit-sliced count of
+// the mismatches of 32 windows, eight positions at a time until none is left.
+__device__ __forceinline__ u32 ah_site_windows(const AhCtx& c, u32 t, u32 p) {
+  // the pattern's fields in vector registers: in scalar ones they would push the
+  // kernel's own into lanes of a further vector register
+  asm volatile("" : "+v"(p));
+  const uint4 set = ah_pat_tab[2 * p], meta = ah_pat_tab[2 * p + 1];
+  const u32 L = meta.x & 0xffu, k = meta.x >> 8, all = 0xffffffffu >> (32u - L);
+  u32 out = ~ah_valid(c, t, L);
+  u32 n[6] = {0u, 0u, 0u, 0u, 0u, 0u};  // bit b of n[i]: bit i of window b's count, at most 32
+#pragma unroll 1
+  for (u32 j0 = 0; j0 < L; j0 += 8u) {
+    uint2 v[8];
+    __builtin_memcpy(v, c.gw + t + j0, sizeof v);  // t < S, j0 + 7 <= 31: in the genome's words and halo
+#if AH_HAS_N
+    u32 nm[8];
+    __builtin_memcpy(nm, c.gn + t + j0, sizeof nm);
+#endif
+#pragma unroll
+    for (u32 e = 0; e < 8; ++e) {
+      const u32 j = j0 + e;
+      const u32 sa = 0u - ((set.x >> j) & 1u), sc = 0u - ((set.y >> j) & 1u),
+                sg = 0u - ((set.z >> j) & 1u), st = 0u - ((set.w >> j) & 1u);
+      u32 x = ~((~(v[e].x | v[e].y) & sa) | (~v[e].x & v[e].y & sc) | (v[e].x & ~v[e].y & sg) |
+                (v[e].x & v[e].y & st));
+#if AH_HAS_N
+      x |= nm[e];
+#endif
+      x &= 0u - ((all >> j) & 1u);
+      out |= x & (0u - ((meta.y >> j) & 1u));
+#pragma unroll
+      for (int i = 0; i < 6; ++i) {
+        const u32 carry = n[i] & x;
+        n[i] ^= x;
+        x = carry;
+      }
+    }
+    u32 more = 0u, same = 0xffffffffu;  // the count against k, from the top bit down
+#pragma unroll
+    for (int i = 5; i >= 0; --i) {
+      const u32 kb = 0u - ((k >> i) & 1u);
+      more |= same & n[i] & ~kb;
+      same &= ~(n[i] ^ kb);
+    }
+    out |= more;  // counts only grow
+    if (out == 0xffffffffu) return 0u;
+  }
+  return ~out;
+}
+
+// Reduces a candidate record to the windows that are sites; false: none is.
+__device__ __forceinline__ bool ah_to_sites(const AhCtx& c, const uint4& e, uint4& m) {
+  uint4 r = make_uint4(0u, 0u, 0u, 0u);
+#pragma unroll 1
+  for (u32 q = 0; q < 4; ++q) {
+    const u32 mq = q == 0u ? m.x : q == 1u ? m.y : q == 2u ? m.z : m.w;
+    if (mq == 0u) continue;
+    const u32 w = mq & ah_site_windows(c, e.y, e.z + q);
+    r.x |= q == 0u ? w : 0u;
+    r.y |= q == 1u ? w : 0u;
+    r.z |= q == 2u ? w : 0u;
+    r.w |= q == 3u ? w : 0u;
+  }
+  m = r;
+  return (r.x | r.y | r.z | r.w) != 0u;
+}
+
+// Patterns of the quad (of its group, from the group's start) at p0.
+__device__ __forceinline__ u32 ah_quad_step(u32 p0) {
+  const u32 left = min(AH_GROUP - p0 % AH_GROUP, AH_PATTERNS - p0);
+  return left < 4u ? left : 4u;
+}
+
+// Windows that are sites of the quad at p0 in word t, as a candidate record's masks.
+__device__ __forceinline__ uint4 ah_quad_sites(const AhCtx& c, u32 t, u32 p0) {
+  const u32 n = ah_quad_step(p0);
+  uint4 m = make_uint4(~0u, n > 1u ? ~0u : 0u, n > 2u ? ~0u : 0u, n > 3u ? ~0u : 0u);
+  (void)ah_to_sites(c, make_uint4(c.g, t, p0, 0u), m);
+  return m;
+}
+
+#if AH_WAVE
+// Wave mode: fills slice s, full after the last tile with `offered` records, again.
+// Returns the records in it, or at least `offered` (above k.slice) when sites' records
+// overfill it.  In that case k.win[s] keeps the windows it had, and the windows
+// dropped here are added: no fewer than the sites dropped.
+__device__ u32 ah_wrefill(const uint2* __restrict__ words, const u32* __restrict__ nmask,
+                          const u64* __restrict__ word_off, const u32* __restrict__ len,
+                          const u64* __restrict__ tile_prefix, u32 n_genomes, const AhCands& k,
+                          u32 wv, u32 lane, u32 s, u32 offered) {
+  uint4* rec = k.out + 2 * (u64)s * k.slice;
+  __threadfence_block();  // the lanes' records are in place
+  // the tile of the last record kept
+  const u32 lg = __builtin_amdgcn_readfirstlane(rec[2 * (u64)(k.slice - 1u)].x);
+  const u32 lt = __builtin_amdgcn_readfirstlane(rec[2 * (u64)(k.slice - 1u)].y) / AH_WTILE;
+  u32 cnt = 0;
+  for (u32 r = 0; r < k.slice; r += 64u) {  // a record moves down, never past one not read yet
+    const u32 i = r + lane;
+    uint4 e = make_uint4(0u, 0u, 0u, 0u), m = e;
+    bool keep = false;
+    if (i < k.slice) {
+      e = rec[2 * (u64)i];
+      m = rec[2 * (u64)i + 1];
+      if (!(e.x == lg && e.y / AH_WTILE == lt))
+        keep = ah_to_sites(ah_ctx(words, nmask, word_off, len, e.x), e, m);
+    }
+    const u64 w = __ballot(keep);
+    if (keep) {
+      const u64 at = cnt + __builtin_amdgcn_mbcnt_hi((u32)(w >> 32), __builtin_amdgcn_mbcnt_lo((u32)w, 0u));
+      rec[2 * at] = e;
+      rec[2 * at + 1] = m;
+    }
+    cnt += (u32)__popcll(w);
+  }
+  const u64 n_tiles = tile_prefix[n_genomes], first = tile_prefix[lg] + lt;
+  u32 lo = 0;
+  for (u64 r = 0;; ++r) {
+    const u64 T = ah_wtile(r, blockIdx.x, wv);
+    if (T >= n_tiles || cnt > k.slice) break;
+    if (T < first) continue;
+    const u32 g = ah_tile_genome(tile_prefix, n_genomes, T, lo);
+    const AhCtx c = ah_ctx(words, nmask, word_off, len, g);
+    const u32 t0 = (u32)(T - tile_prefix[g]) * AH_WTILE + lane * (u32)AH_U;
+    for (u32 u = 0; u < (u32)AH_U; ++u) {
+      const u32 t = lane < 63u ? t0 + u : 0xffffffffu;
+      for (u32 p0 = 0; p0 < AH_PATTERNS; p0 += ah_quad_step(p0)) {
+        uint4 m = make_uint4(0u, 0u, 0u, 0u);
+        if (t < c.S) m = ah_quad_sites(c, t, p0);
+        cnt = ah_wcand(c, k, t, p0, m.x, m.y, m.z, m.w, cnt, s);
+      }
+    }
+  }
+  if (cnt > k.slice) return max(cnt, offered);
+  if (lane == 0) k.win[s] = 0;  // nothing is dropped after all
+  __builtin_amdgcn_s_waitcnt(AH_WAIT_VMCNT0);
+  return cnt;
+}
+#else
+// Tile mode: the workgroup fills its slice, full after the last tile, again.  Afterwards
+// ah_n_cand is the records in it, or no less than it was (above k.slice) when
+// sites' records overfill it; ah_n_lost then keeps the windows it had, and the
+// windows dropped here are added: no fewer than the sites dropped.
+__device__ void ah_refill(const uint2* __restrict__ words, const u32* __restrict__ nmask,
+                          const u64* __restrict__ word_off, const u32* __restrict__ len,
+                          const u64* __restrict__ tile_prefix, u32 n_genomes, const AhCands& k) {
+  uint4* rec = k.out + 2 * (u64)blockIdx.x * k.slice;
+  const u32 offered = ah_n_cand;
+  __threadfence_block();
+  __syncthreads();  // the threads' records are in place, and all have read ah_n_cand
+  // the tile of the last record kept
+  const u32 lg = rec[2 * (u64)(k.slice - 1u)].x, lt = rec[2 * (u64)(k.slice - 1u)].y / (u32)AH_TILE;
+  if (threadIdx.x == 0) ah_n_cand = 0;
+  for (u32 r = 0; r < k.slice; r += AH_BLOCK) {  // a record moves down, never past one not read yet
+    const u32 i = r + threadIdx.x;
+    uint4 e = make_uint4(0u, 0u, 0u, 0u), m = e;
+    bool keep = false;
+    if (i < k.slice) {
+      e = rec[2 * (u64)i];
+      m = rec[2 * (u64)i + 1];
+      if (!(e.x == lg && e.y / (u32)AH_TILE == lt))
+        keep = ah_to_sites(ah_ctx(words, nmask, word_off, len, e.x), e, m);
+    }
+    __syncthreads();  // these records are read
+    if (keep) {
+      const u64 at = atomicAdd(&ah_n_cand, 1u);
+      rec[2 * at] = e;
+      rec[2 * at + 1] = m;
+    }
+  }
+  __threadfence_block();
+  __syncthreads();
+  const u64 n_tiles = tile_prefix[n_genomes];
+  u32 lo = 0;
+  for (u64 T = tile_prefix[lg] + lt; T < n_tiles; T += gridDim.x) {
+    const bool over = ah_n_cand > k.slice;
+    __syncthreads();  // all have read it
+    if (over) break;
+    const u32 g = ah_tile_genome(tile_prefix, n_genomes, T, lo);
+    const AhCtx c = ah_ctx(words, nmask, word_off, len, g);
+    const u32 t0 = (u32)(T - tile_prefix[g]) * (u32)AH_TILE + threadIdx.x * (u32)AH_U;
+    for (u32 t = t0; t < min(t0 + (u32)AH_U, c.S); ++t)
+      for (u32 p0 = 0; p0 < AH_PATTERNS; p0 += ah_quad_step(p0)) {
+        const uint4 m = ah_quad_sites(c, t, p0);
+        if ((m.x | m.y | m.z | m.w) != 0u) ah_cand(c, k, t, p0, m.x, m.y, m.z, m.w);
+      }
+    __syncthreads();
+  }
+  if (threadIdx.x == 0) {
+    if (ah_n_cand > k.slice)
+      ah_n_cand = max(ah_n_cand, offered);
+    else
+      ah_n_lost = 0;  // nothing is dropped after all
+  }
+  __syncthreads();
+}
+#endif
+#endif
+
+#if AH_WAVE
 extern "C" __global__ __launch_bounds__(AH_BLOCK) void ah_scan_kernel(
     const uint2* __restrict__ words, const u32* __restrict__ nmask,
     const u64* __restrict__ word_off, const u32* __restrict__ len,
@@ -550,6 +771,10 @@ extern "C" __global__ __launch_bounds__(AH_BLOCK) void ah_scan_kernel(
     cnt = ah_wgroups((ah_lds_uint2*)my + (cur.t0 & 1u), cur.t0, cur.c, k, lane, my, nx, cnt, s);
     cur = nx;
   }
+#if AH_REFILL
+  if (cnt > slice)
+    cnt = ah_wrefill(words, nmask, word_off, len, tile_prefix, n_genomes, k, wv, lane, s, cnt);
+#endif
   // the exact count of this wave's candidates (records written by its own
   // lanes: the fence orders their stores before the loads)
   __threadfence_block();
@@ -618,6 +843,10 @@ extern "C" __global__ __launch_bounds__(AH_BLOCK) void ah_scan_kernel(
     ah_groups((ah_lds_uint2*)tile, t0, c, k);
     __syncthreads();                // nobody reads the tile any more
   }
+#if AH_REFILL
+  if (ah_n_cand > slice)  // the same in every thread, after the tile's barrier
+    ah_refill(words, nmask, word_off, len, tile_prefix, n_genomes, k);
+#endif
 #if AH_TILE_COUNT
   // the exact count of the workgroup's candidates (records written by its
   // own threads: the fence and the barrier order their stores before the
