@@ -1656,14 +1656,13 @@ bool carve_seg(const ScanWs& w, uint32_t n_genomes, uint64_t n_seg, uint64_t cap
   // 64-pair panel 8.45 ms against 8.57).
   sg.wide = cap > 131072 && expected > 32768.0;
   sg.t_n = cap > 131072 ? 512 : 128;
-  sg.t_seg = sg.wide ? 1024 : 128;
   // The grid, and the look-back words cleared for every query, do not follow
   // roomy buffers without end: past kTiles the tiles grow with the count (16
   // references with room for 50 M sites took 51.7 us a query with a tile for each
   // 512 of them, 35.0 with room for 65,536).
   const uint32_t max_tiles = sg.wide ? ah::kTilesWide : ah::kTilesNarrow;
   sg.n_tiles = (uint32_t)std::min<uint64_t>(
-      {std::max<uint64_t>(1024, (cap + sg.t_n - 1) / sg.t_n), cap / 32 + 1, max_tiles});
+      {std::max<uint64_t>(1024, (cap + sg.t_n - 1) / sg.t_n), cap / 16 + 1, max_tiles});
   sg.n_zero = (uint32_t)(2 * n_seg + 2 * (uint64_t)sg.n_tiles);
   sg.cnt = c.take<uint32_t>(sg.n_zero);  // counts, fill counters, look-back words
   sg.fill = sg.cnt + n_seg;
@@ -1807,13 +1806,13 @@ ah_status launch_scan_kernel(const ScanFns& fn, Tuning tn, const ah_genomes* g, 
       uint64_t cap = capacity;
       uint64_t* cstat = w.cstat;
       uint64_t *tile_base = seg->tile_base, *tile_meta = seg->tile_meta;
-      uint32_t *tile_seg = seg->tile_seg, t_n = seg->t_n, t_seg = seg->t_seg;
+      uint32_t *tile_seg = seg->tile_seg, t_n = seg->t_n;
       uint32_t n_tiles = seg->n_tiles;
       void* sargs[] = {&words,      &nmask,       &word_off, &len,      &ccands,
                        &slice,      &cslice_cnt,  &cslice_tot, &cslice_win, &ccand_sites,
                        &cseg_cnt,   &n_seg,       &seg_n,    &seg_off,  &seg_fill,
                        &out,        &cap,         &d_res,    &cstat,    &tile_base,
-                       &tile_seg,   &tile_meta,   &t_n,      &t_seg,    &n_tiles};
+                       &tile_seg,   &tile_meta,   &t_n,      &n_tiles};
       AH_HIP(hipModuleLaunchKernel(fn.emit_seg, grid, 1, 1, ah::kBlock, 1, 1, 0, st, sargs,
                                    nullptr));
       return AH_OK;

@@ -160,8 +160,7 @@ struct SegBuffers {
   uint64_t* tile_base;  // [n_tiles + 1] first site of each tile
   uint32_t* tile_seg;   // [n_tiles + 1] first segment of each tile
   uint64_t* tile_meta;  // [2] tiles, sites
-  uint32_t t_n, t_seg;  // bounds of the sites per tile (from the count, from the mean segment)
-                        // while n_tiles of them hold the count
+  uint32_t t_n;         // bound of the sites per tile while n_tiles of them hold the count
   uint32_t n_tiles;     // tiles at most, whatever the count
   uint32_t n_zero;         // uint32 words to clear, from cnt on
   bool wide;               // workgroups of 256 threads (else of one wave)

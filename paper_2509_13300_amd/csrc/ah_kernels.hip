@@ -1838,10 +1838,14 @@ __global__ __launch_bounds__(kB) void k_query_tail(SegArgs A) {
   }
   if (b >= nt) return;
   const u32 m = (u32)(base1 - base);
-  if (m == 0) {
+  if (m == 0) {  // no segment starts here: only the last tile needs to wait for those before it
     if (sites_ok && wv == 0) {
-      const u64 before = seg_lookback(A.lb, b, 0ull);
-      if (b + 1 == nt && t == 0) seg_result(A, before);
+      if (b + 1 < nt) {
+        if (t == 0) lb_store(&A.lb[b], kLbAgg);
+      } else {
+        const u64 before = seg_lookback(A.lb, b, 0ull);
+        if (t == 0) seg_result(A, before);
+      }
     }
     return;
   }

@@ -1070,9 +1070,8 @@ extern "C" __global__ __launch_bounds__(AH_BLOCK) void ah_emit_kernel(
 // on seg_fill[segment] (cleared before the filter).  The order inside a segment
 // is left to the sort that follows.  Workgroup 0 also writes the segments'
 // first slots (seg_off, n_seg + 1 entries) and the tail's tiles (T sites, T
-// from the count: about a thousand tiles, of at least 32 sites and at most t_n,
-// or the mean segment up to t_seg, so that few tiles hold no segment; larger
-// where n_tiles of them would not hold every site), the result and the
+// from the count: about a thousand tiles, of at least 16 sites and at most t_n;
+// larger where n_tiles of them would not hold every site), the result and the
 // candidate-list statistics, as the slice-order emit does.
 // Nothing is written when the sites overflow the capacity.
 #define AH_SEG_MAX 4096
@@ -1084,7 +1083,7 @@ extern "C" __global__ __launch_bounds__(AH_BLOCK) void ah_emit_seg_kernel(
     const u32* __restrict__ cand_sites, const u32* __restrict__ seg_cnt, u32 n_seg, u32 seg_n,
     u64* __restrict__ seg_off, u32* __restrict__ seg_fill, AhHitRec* __restrict__ out, u64 cap,
     AhResult* __restrict__ res, u64* __restrict__ cand_stat, u64* __restrict__ tile_base,
-    u32* __restrict__ tile_seg, u64* __restrict__ tile_meta, u32 t_n, u32 t_seg, u32 n_tiles) {
+    u32* __restrict__ tile_seg, u64* __restrict__ tile_meta, u32 t_n, u32 n_tiles) {
   __shared__ u64 s_off[AH_SEG_MAX + 1];
   __shared__ u64 tmp[AH_BLOCK / 64];
   // this thread's first candidate, in flight while the slots are summed
@@ -1129,9 +1128,8 @@ extern "C" __global__ __launch_bounds__(AH_BLOCK) void ah_emit_seg_kernel(
     // The tail's tiles: tile b starts at the first segment at or past site b T.
     // Workgroup 0 writes them with the segments' first slots; above AH_SEG_MAX
     // segments the grid does.
-    u64 T = 32;
+    u64 T = 16;
     while (T < t_n && T * 1024 < found) T <<= 1;
-    while (T < t_seg && T * n_seg < found) T <<= 1;
     while (T * n_tiles < found) T <<= 1;  // more sites than n_tiles tiles of t_n hold
     const u64 nt = found ? (found + T - 1) / T : 1;
     const u32 q0 = big ? blockIdx.x * AH_BLOCK + threadIdx.x : blockIdx.x ? n_seg + 1 : threadIdx.x;
