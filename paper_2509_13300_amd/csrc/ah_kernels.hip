@@ -1573,7 +1573,9 @@ __device__ __forceinline__ u32 seg_count(const C* pc, uint2 r) {
 // gave up on.
 constexpr u64 kLbAgg = 1ull << 62, kLbIncl = 2ull << 62, kLbErr = 1ull << 61;
 constexpr u64 kLbVal = (1ull << 61) - 1ull;
-constexpr u32 kLbPolls = 1u << 20;  // polls of one window before a wait gives up
+// Polls of one window before a wait gives up: several seconds, as a tile of
+// millions of sites takes tenths of one.
+constexpr u32 kLbPolls = 1u << 23;
 
 __device__ __forceinline__ u64 lb_load(const u64* p) {
   return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -2694,6 +2696,15 @@ hipError_t launch_seg_tail(ah_hit* staged, ah_hit* out, uint64_t hcap, const Seg
       k_query_tail<true, 256, 4096><<<sg.n_tiles, 256, 0, st>>>(A);
     else
       k_query_tail<false, 256, 4096><<<sg.n_tiles, 256, 0, st>>>(A);
+  } else if (sg.n_seg > kSegEmitMax) {
+    // Among many segments one may be long (a repeat in one of thousands of contigs),
+    // and its workgroup holds up every tile after it: four waves take 4,000 such sites
+    // in 335 us a query where one takes 913 (the radix sort 170), and 20,000 contigs
+    // without any in 140 where one takes 138.5 (213).
+    if (exact)
+      k_query_tail<true, 256, 1024><<<sg.n_tiles, 256, 0, st>>>(A);
+    else
+      k_query_tail<false, 256, 1024><<<sg.n_tiles, 256, 0, st>>>(A);
   } else {
     if (exact)
       k_query_tail<true, 64, 1024><<<sg.n_tiles, 64, 0, st>>>(A);
