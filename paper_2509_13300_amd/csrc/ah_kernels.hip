@@ -267,8 +267,10 @@ __device__ __forceinline__ u64 run_prefix(u32 n, const ValF& val, const PutF& pu
     const u64 y = __shfl_up(x, o, 64);
     if (lane >= o) x += y;
   }
+  if (r0 != 0u) {  // the first run has none before it
 #pragma unroll
-  for (u32 o = 32; o > 0; o >>= 1) before += __shfl_xor(before, o, 64);
+    for (u32 o = 32; o > 0; o >>= 1) before += __shfl_xor(before, o, 64);
+  }
   if (lane == 63) {
     wsum[0][w] = x;
     wsum[1][w] = before;
@@ -305,7 +307,8 @@ __global__ __launch_bounds__(kSmallBlock) void k_tile_prefix_small(const u32* __
   const u32 runs = (n + kRun - 1) / kRun;
   if (blockIdx.x >= runs) return;
   const u64 upto = run_prefix(
-      n, [&](u32 g) { return (u32)((((u64)len[g] + 31) / 32 + tile_words - 1) / tile_words); },
+      // words of a genome: at most 2^27, and a 32-bit division
+      n, [&](u32 g) { return ((u32)(((u64)len[g] + 31) >> 5) + tile_words - 1u) / tile_words; },
       [&](u32 g, u64 at) { prefix[g] = at; });
   if (threadIdx.x == 0 && blockIdx.x + 1 == runs) {
     prefix[n] = upto;

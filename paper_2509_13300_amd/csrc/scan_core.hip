@@ -1068,11 +1068,11 @@ extern "C" __global__ __launch_bounds__(AH_BLOCK) void ah_emit_kernel(
 // AH_SEG_MAX segments, read from seg_off above), at the place inside it that
 // the count reserved (AH_QUAD_ONE_PAIR) or one taken here with a device atomic
 // on seg_fill[segment] (cleared before the filter).  The order inside a segment
-// is left to the sort that follows.  Workgroup 0 also writes the segments'
+// is left to the sort that follows.  The last workgroup also writes the segments'
 // first slots (seg_off, n_seg + 1 entries) and the tail's tiles (T sites, T
 // from the count: about a thousand tiles, of at least 16 sites and at most t_n;
-// larger where n_tiles of them would not hold every site), the result and the
-// candidate-list statistics, as the slice-order emit does.
+// larger where n_tiles of them would not hold every site), workgroup 0 the result
+// and the candidate-list statistics, as the slice-order emit does.
 // Nothing is written when the sites overflow the capacity.
 #define AH_SEG_MAX 4096
 extern "C" __global__ __launch_bounds__(AH_BLOCK) void ah_emit_seg_kernel(
@@ -1126,24 +1126,24 @@ extern "C" __global__ __launch_bounds__(AH_BLOCK) void ah_emit_seg_kernel(
   }
   {
     // The tail's tiles: tile b starts at the first segment at or past site b T.
-    // Workgroup 0 writes them with the segments' first slots; above AH_SEG_MAX
-    // segments the grid does.
-    u64 T = 16;
-    while (T < t_n && T * 1024 < found) T <<= 1;
-    while (T * n_tiles < found) T <<= 1;  // more sites than n_tiles tiles of t_n hold
-    const u64 nt = found ? (found + T - 1) / T : 1;
-    const u32 q0 = big ? blockIdx.x * AH_BLOCK + threadIdx.x : blockIdx.x ? n_seg + 1 : threadIdx.x;
+    // The last workgroup writes them with the segments' first slots (the first has
+    // the statistics); above AH_SEG_MAX segments the grid does.
+    u32 sh = 4;  // T = 2^sh
+    while ((1u << sh) < t_n && (1024ull << sh) < found) ++sh;
+    while (((u64)n_tiles << sh) < found) ++sh;  // more sites than n_tiles tiles of t_n hold
+    const u64 nt = found ? (found + (1ull << sh) - 1) >> sh : 1;
+    const u32 q0 = big ? blockIdx.x * AH_BLOCK + threadIdx.x : blockIdx.x + 1 < gridDim.x ? n_seg + 1 : threadIdx.x;
     for (u32 q = q0; q <= n_seg; q += big ? gridDim.x * AH_BLOCK : AH_BLOCK) {
       const u64 o = big ? seg_off[q] : s_off[q];
       const u64 prev = q ? (big ? seg_off[q - 1] : s_off[q - 1]) : 0;
       if (!big) seg_off[q] = o;
       if (found <= cap)
-        for (u64 b = q ? prev / T + 1 : 0; b * T <= o && b < nt; ++b) {
+        for (u64 b = q ? (prev >> sh) + 1 : 0; (b << sh) <= o && b < nt; ++b) {
           tile_base[b] = o;
           tile_seg[b] = q;
         }
     }
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
+    if (blockIdx.x + 1 == gridDim.x && threadIdx.x == 0) {
       tile_meta[0] = nt;
       tile_meta[1] = found;
       if (found <= cap) {
