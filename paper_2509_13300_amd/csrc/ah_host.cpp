@@ -1662,7 +1662,7 @@ bool carve_seg(const ScanWs& w, uint32_t n_genomes, uint64_t n_seg, uint64_t cap
   // 512 of them, 35.0 with room for 65,536).
   const uint32_t max_tiles = sg.wide ? ah::kTilesWide : ah::kTilesNarrow;
   sg.n_tiles = (uint32_t)std::min<uint64_t>(
-      {std::max<uint64_t>(1024, (cap + sg.t_n - 1) / sg.t_n), cap / 16 + 1, max_tiles});
+      {std::max<uint64_t>(1024, (cap + sg.t_n - 1) / sg.t_n), cap + 1, max_tiles});
   sg.n_zero = (uint32_t)(2 * n_seg + 2 * (uint64_t)sg.n_tiles);
   sg.cnt = c.take<uint32_t>(sg.n_zero);  // counts, fill counters, look-back words
   sg.fill = sg.cnt + n_seg;
