@@ -2590,8 +2590,7 @@ ah_status ah_scan_prepare(const ah_primer_pair* pairs, uint32_t n_pairs, int has
   ah_status s = compile_pairs(pairs, n_pairs, ps);
   if (s) return s;
   ScanFns fn;
-  return get_scan_kernel(gen_program(patterns_of(ps), has_nmask != 0, tuning_for(pairs, n_pairs)),
-                         fn);
+  return scan_kernels_for(pairs, n_pairs, ps, has_nmask != 0, tuning_for(pairs, n_pairs), fn);
 }
 
 ah_status ah_set_scan_tuning(const ah_primer_pair* pairs, uint32_t n_pairs,
