@@ -519,42 +519,33 @@ __device__ __forceinline__ u64 ah_wtile(u64 r, u32 b, u32 wv) {
 // on 300 genomes: 115 us a query, 124).
 
 // Windows of word t of genome c that are sites of pattern p: a bit-sliced count of
-// the mismatches of 32 windows, eight positions at a time until none is left.
+// the mismatches of 32 windows, until none is left.  (In a loop: unrolled by
+// eight, a program of one pair took 2.2 s to compile instead of 1.7.)
 __device__ __forceinline__ u32 ah_site_windows(const AhCtx& c, u32 t, u32 p) {
   // the pattern's fields in vector registers: in scalar ones they would push the
   // kernel's own into lanes of a further vector register
   asm volatile("" : "+v"(p));
   const uint4 set = ah_pat_tab[2 * p], meta = ah_pat_tab[2 * p + 1];
-  const u32 L = meta.x & 0xffu, k = meta.x >> 8, all = 0xffffffffu >> (32u - L);
+  const u32 L = meta.x & 0xffu, k = meta.x >> 8;
   u32 out = ~ah_valid(c, t, L);
   u32 n[6] = {0u, 0u, 0u, 0u, 0u, 0u};  // bit b of n[i]: bit i of window b's count, at most 32
 #pragma unroll 1
-  for (u32 j0 = 0; j0 < L; j0 += 8u) {
-    uint2 v[8];
-    __builtin_memcpy(v, c.gw + t + j0, sizeof v);  // t < S, j0 + 7 <= 31: in the genome's words and halo
+  for (u32 j = 0; j < L; ++j) {  // t < S and j <= 31: in the genome's words and halo
+    const uint2 v = c.gw[t + j];
+    const u32 sa = 0u - ((set.x >> j) & 1u), sc = 0u - ((set.y >> j) & 1u),
+              sg = 0u - ((set.z >> j) & 1u), st = 0u - ((set.w >> j) & 1u);
+    u32 x = ~((~(v.x | v.y) & sa) | (~v.x & v.y & sc) | (v.x & ~v.y & sg) | (v.x & v.y & st));
 #if AH_HAS_N
-    u32 nm[8];
-    __builtin_memcpy(nm, c.gn + t + j0, sizeof nm);
+    x |= c.gn[t + j];
 #endif
+    out |= x & (0u - ((meta.y >> j) & 1u));
 #pragma unroll
-    for (u32 e = 0; e < 8; ++e) {
-      const u32 j = j0 + e;
-      const u32 sa = 0u - ((set.x >> j) & 1u), sc = 0u - ((set.y >> j) & 1u),
-                sg = 0u - ((set.z >> j) & 1u), st = 0u - ((set.w >> j) & 1u);
-      u32 x = ~((~(v[e].x | v[e].y) & sa) | (~v[e].x & v[e].y & sc) | (v[e].x & ~v[e].y & sg) |
-                (v[e].x & v[e].y & st));
-#if AH_HAS_N
-      x |= nm[e];
-#endif
-      x &= 0u - ((all >> j) & 1u);
-      out |= x & (0u - ((meta.y >> j) & 1u));
-#pragma unroll
-      for (int i = 0; i < 6; ++i) {
-        const u32 carry = n[i] & x;
-        n[i] ^= x;
-        x = carry;
-      }
+    for (int i = 0; i < 6; ++i) {
+      const u32 carry = n[i] & x;
+      n[i] ^= x;
+      x = carry;
     }
+    if ((j & 3u) != 3u && j + 1u < L) continue;
     u32 more = 0u, same = 0xffffffffu;  // the count against k, from the top bit down
 #pragma unroll
     for (int i = 5; i >= 0; --i) {
