@@ -243,7 +243,8 @@ size_t ah_scan_workspace_bytes(const ah_genomes* genomes, const ah_primer_pair* 
  * fGC is the oligo's G+C fraction, so under 6 and 7 the maximum runs over
  * oligos that pair the site alike too (the best member at each unpaired
  * degenerate position).  Concentrations in M inside the logarithms.  Sums
- * are FP32 with compensation; the salt and logarithm terms are FP64.
+ * of stacks are exact (fixed point), the terminal pairs, salt and logarithm
+ * terms FP64, and Delta-H over the denominator an FP32 quotient.
  * ------------------------------------------------------------------------- */
 typedef struct ah_tm_params {
   double dnac1_nM, dnac2_nM, Na_mM, K_mM, Tris_mM, Mg_mM, dNTPs_mM;

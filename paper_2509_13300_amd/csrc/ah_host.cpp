@@ -1639,12 +1639,12 @@ ah_status check_genomes(const ah_genomes* g) {
 
 // Segment buffers of ah_query, carved from the workspace's radix-sort
 // buffers, which its segmented tail does not use.  False when the segments
-// are more than kSegMax, their sort keys too wide, or the buffers do not fit.
+// are more than kSegMax or the buffers do not fit.
 bool carve_seg(const ScanWs& w, uint32_t n_genomes, uint64_t n_seg, uint64_t cap, double expected,
-               const ah::KeyBits& kb, ah::SegBuffers& sg) {
+               ah::SegBuffers& sg) {
   if (n_seg == 0 || n_seg > ah::kSegMax) return false;
-  // a tile's keys: its segments, pos << 2 | strand-primer, 12 bits of index
-  if (bits_for(n_seg - 1) + kb.pb + 2 + 12 > 63) return false;
+  // a tile's keys in 63 bits: its segments, pos << 2 | strand-primer, 12 bits of index
+  static_assert(ah::kSegMax == 1u << 17, "17 + (32 + 2) + 12 bits");
   const uintptr_t beg = (uintptr_t)w.sb.keys[0];
   const uintptr_t end = (uintptr_t)w.sb.hist[2] +
                         (uintptr_t)ah::kSortDigits * w.sb.hstride * sizeof(uint32_t);
@@ -2451,7 +2451,7 @@ ah_status ah_query(const ah_genomes* g, const ah_primer_pair* pairs, const ah_wi
   ah::SegBuffers sg{};
   double expected = 0.0;
   if (g->n > 0 && seg_mode(pairs, n_pairs, g->n, g->max_len, &expected) &&
-      carve_seg(w, g->n, (uint64_t)n_pairs * g->n, hit_capacity, expected, kb, sg)) {
+      carve_seg(w, g->n, (uint64_t)n_pairs * g->n, hit_capacity, expected, sg)) {
     // each segment (pair, genome) sorted, its Tm and amplicons, by one workgroup
     s = launch_scan_kernel(fn, tn, g, w, d_hit_res, hit_capacity, st, nullptr, &sg);
     if (s) return s;

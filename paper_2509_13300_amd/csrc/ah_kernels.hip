@@ -1565,12 +1565,6 @@ __device__ __forceinline__ uint2 seg_range(const PosF& P, u32 m, u32 pos, u32 lb
   return make_uint2(a, b < a ? a : b);
 }
 
-// Wanted sites in [r.x, r.y) from inclusive counts pc.
-template <class C>
-__device__ __forceinline__ u32 seg_count(const C* pc, uint2 r) {
-  return (r.y ? (u32)pc[r.y - 1] : 0u) - (r.x ? (u32)pc[r.x - 1] : 0u);
-}
-
 // Look-back words: (state << 62) | value, state 1: the tile's own amplicons,
 // 2: those of it and every earlier tile; kLbErr marks a prefix that a wait
 // gave up on.
