@@ -693,7 +693,7 @@ FilterPlan plan_filter_uncached(const Pattern& p, bool allow, double weight) {
 }
 
 // The plan of a pattern, memoised by everything it depends on: the local
-// search takes 0.5-11 ms a pair, and the sizing calls (scan workspaces, every
+// search takes 0.4-2.3 ms a pair, and the sizing calls (scan workspaces, every
 // part of a serving job) ask for the same patterns again and again.  A burst
 // of 8 one-pair jobs, whose parts are sized under the server's lock, took
 // 24.6 ms with the search repeated and takes 0.9 ms with it kept.  Bounded: a
@@ -1649,15 +1649,16 @@ bool carve_seg(const ScanWs& w, uint32_t n_genomes, uint64_t n_seg, uint64_t cap
   const uintptr_t end = (uintptr_t)w.sb.hist[2] +
                         (uintptr_t)ah::kSortDigits * w.sb.hstride * sizeof(uint32_t);
   Carver c((void*)beg, (size_t)(end - beg));
-  // Workgroups of one wave pass tiles of a few dozen sites through with no
-  // barrier (16 references 34.2 us a query against 36.1, 20,000 contigs with
-  // 18,000 sites 144 against 156).  Where tens of thousands of random sites are
-  // expected and there is room for more than 2^17, tiles of hundreds (430,000 sites of a
-  // 64-pair panel 8.45 ms against 8.57).
+  // Small tiles: a few dozen sites pass through one wave with no barrier (16
+  // references 34.2 us a query against 36.1 in workgroups of 256 threads; the
+  // launch takes four waves above kSegEmitMax segments).  Where tens of
+  // thousands of random sites are expected and there is room for more than
+  // 2^17, tiles of hundreds (430,000 sites of a 64-pair panel 8.45 ms against
+  // 8.57).
   sg.wide = cap > 131072 && expected > 32768.0;
   sg.t_n = cap > 131072 ? 512 : 128;
   // The grid, and the look-back words cleared for every query, do not follow
-  // roomy buffers without end: past kTiles the tiles grow with the count (16
+  // roomy buffers without end: past max_tiles the tiles grow with the count (16
   // references with room for 50 M sites took 51.7 us a query with a tile for each
   // 512 of them, 35.0 with room for 65,536).
   const uint32_t max_tiles = sg.wide ? ah::kTilesWide : ah::kTilesNarrow;

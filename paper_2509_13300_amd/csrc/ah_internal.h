@@ -136,9 +136,9 @@ hipError_t launch_sort_tm_mark(ah_hit* staged, ah_hit* out, const uint64_t* n_de
 // The tail of ah_query over at most kSegMax segments (pair, genome), after
 // the scan's segmented emit has put each segment's sites at
 // off[s] .. off[s + 1] of the staging area in no particular order: one
-// launch, a workgroup per tile (the segments whose first site is one of `tile`
+// launch, a workgroup per tile (the segments whose first site is one of T
 // consecutive sites), puts the tile into canonical order (in LDS up to 4,096
-// sites, 1,024 for the one-wave form), computes the Tm of every site, counts
+// sites where `wide` is set, else 1,024), computes the Tm of every site, counts
 // the amplicons each leader + site starts, takes the amplicons of the earlier
 // tiles by a look-back over lb, and writes its own.
 // key_bits: bits of pos << 2 | strand-primer; hcap: the capacity of out.
@@ -163,7 +163,8 @@ struct SegBuffers {
   uint32_t t_n;         // bound of the sites per tile while n_tiles of them hold the count
   uint32_t n_tiles;     // tiles at most, whatever the count
   uint32_t n_zero;         // uint32 words to clear, from cnt on
-  bool wide;               // workgroups of 256 threads (else of one wave)
+  bool wide;               // four waves and 4,096 sites in LDS (else 1,024; one wave up to
+                           // kSegEmitMax segments, four above)
 };
 // off from cnt, when n_seg > kSegEmitMax (up to it, the emit pass does it).
 hipError_t launch_seg_prefix(const SegBuffers& sg, hipStream_t st);

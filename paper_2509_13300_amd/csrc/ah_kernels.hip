@@ -294,7 +294,7 @@ __device__ __forceinline__ u64 run_prefix(u32 n, const ValF& val, const PutF& pu
 // entries), the result reset, and the clearing of `zero` and `zero64` (every
 // workgroup a part; those past the genomes' runs only clear: the words of a
 // query's segments and tiles may be many more than its genomes).  20,000
-// genomes: 11 us (29 us by one workgroup, 20 values a thread; six launches and
+// genomes: 10 us (29 us by one workgroup, 20 values a thread; six launches and
 // 20 us as a scan in three with the clearing apart).
 __global__ __launch_bounds__(kSmallBlock) void k_tile_prefix_small(const u32* __restrict__ len, u32 n,
                                                                    u32 tile_words,

@@ -882,7 +882,7 @@ extern "C" __global__ __launch_bounds__(AH_BLOCK) void ah_verify_kernel(
   // dropped).  The grid also clears the sort's first two histogram tables
   // (the emit pass counts into the first, the first sort pass into the
   // second).  With seg_cnt set, the sites are also counted per segment
-  // (pair, genome) at seg_cnt[pair * seg_n + genome]; when every record's
+  // (pair, genome) at seg_cnt[ah_seg_slot(...)]; when every record's
   // patterns share a pair, one device atomic per candidate reserves its
   // sites' places in the segment, and cand_sites keeps the first place + 1
   // (0: no sites) for the segmented emit instead of the count.
