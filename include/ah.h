@@ -348,7 +348,8 @@ size_t ah_pair_workspace_bytes(uint64_t hit_capacity, uint32_t n_pairs);
  * 1,024 sites, or 4,096 where many are expected), computes their
  * Tm, counts the amplicons each + site starts, takes its first amplicon slot
  * from the counts of the earlier tiles and writes its amplicons.  With more
- * segments, when a pair is expected to give more than 512 sites on the longest
+ * segments, with more than 4,096 of them and a genome longer than 2^24 bases,
+ * when a pair is expected to give more than 512 sites on the longest
  * genome (random bases, both primers and strands), or with
  * AH_QUERY_SEGMENTED=0 in the environment (=1 forces the segmented tail), the
  * sites go through the radix sort instead, the Tm is computed by extra

@@ -1685,6 +1685,12 @@ bool carve_seg(const ScanWs& w, uint32_t n_genomes, uint64_t n_seg, uint64_t cap
 // strands) decide, against kSegExpected; AH_QUERY_SEGMENTED=1 or 0 forces one
 // tail (the segmented one still only up to kSegMax segments).
 constexpr double kSegExpected = 512.0;
+// Random sites are not all: a family of repeats may give one genome 10^4 sites and
+// more, and among thousands of segments the tiles after it wait for the one
+// workgroup that sorts them (16,000 in a 17-Mbp genome among 5,000 contigs: 1.45
+// against 0.25 ms).  Above kSegEmitMax segments a genome longer than any
+// prokaryote's takes the radix tail.
+constexpr uint32_t kSegGenome = 1u << 24;
 // *expected: the random sites of all pairs on n genomes of that length.
 bool seg_mode(const ah_primer_pair* pairs, uint32_t n_pairs, uint32_t n, uint32_t max_len,
               double* expected) {
@@ -1698,7 +1704,9 @@ bool seg_mode(const ah_primer_pair* pairs, uint32_t n_pairs, uint32_t n, uint32_
     sum += rate * (double)max_len * (double)n;
   }
   *expected = sum;
-  return (e && e[0] == '1') || most <= kSegExpected;
+  if (e && e[0] == '1') return true;
+  if ((uint64_t)n_pairs * n > ah::kSegEmitMax && max_len > kSegGenome) return false;
+  return most <= kSegExpected;
 }
 
 // Reset of d_res, tile counts and prefix, then the filter, the exact count
