@@ -1061,8 +1061,8 @@ extern "C" __global__ __launch_bounds__(AH_BLOCK) void ah_emit_kernel(
 // on seg_fill[segment] (cleared before the filter).  The order inside a segment
 // is left to the sort that follows.  The last workgroup also writes the segments'
 // first slots (seg_off, n_seg + 1 entries) and the tail's tiles (T sites, T
-// from the count: at most a thousand tiles, as small as that allows and of at most
-// t_n sites; larger where n_tiles of them would not hold every site), workgroup 0 the result
+// from the count: one tile up to 16 sites, else at most a thousand, as small as that
+// allows and of at most t_n sites; larger where n_tiles of them would not hold every site), workgroup 0 the result
 // and the candidate-list statistics, as the slice-order emit does.
 // Nothing is written when the sites overflow the capacity.
 #define AH_SEG_MAX 4096
@@ -1122,8 +1122,11 @@ extern "C" __global__ __launch_bounds__(AH_BLOCK) void ah_emit_seg_kernel(
     // as its sites' pairings, so a few sites are spread out (894 sites of two pairs
     // and their decoys on 185 contigs: 69 us a query, 91 in tiles of 32 and more), up
     // to a thousand tiles: of 113,000 sites on 3,000 genomes, twice as many took 251 us
-    // a query and four times 297, against 217.
-    u32 sh = 0;  // T = 2^sh
+    // a query and four times 297, against 217.  Up to 16 sites stay in one tile, which
+    // waits for none (8 sites of 16 references 34.0 us a query, 35.0 in tiles of
+    // their own; over 52 queries of 2-222 sites 0.2% faster, up to 32 sites
+    // 1.1% slower, up to 64 1.4%).
+    u32 sh = found <= 16u ? 4u : 0u;  // T = 2^sh
     while ((1u << sh) < t_n && (1024ull << sh) < found) ++sh;
     while (((u64)n_tiles << sh) < found) ++sh;  // more sites than n_tiles tiles of t_n hold
     const u64 nt = found ? (found + (1ull << sh) - 1) >> sh : 1;

@@ -97,3 +97,33 @@ def test_more_sites_than_the_tiles_hold(dev, form):
     assert out[0][0]["count"] > least and out[0][1]["count"] > 0
     assert out[0][:2] == out[1][:2]
     assert torch.equal(out[0][2], out[1][2]) and torch.equal(out[0][3], out[1][3])
+
+
+@pytest.mark.parametrize("count", [1, 2, 15, 16, 17, 33])
+def test_sites_around_the_single_tile(dev, count):
+    """Up to 16 sites are one tile, more a tile a segment: two sites a genome, an amplicon
+    each, as the three calls give them."""
+    import torch
+
+    from paper_2509_13300_amd import path
+
+    pair = plan.PairSpec("ACGTTGCAAGCTTCGAGGTC", "TTGACCATGCAGGTATCCGA", k=0, clamp=0, min_len=100, max_len=400)
+    n, length = 20, 3000
+    g = torch.Generator(device=dev)
+    g.manual_seed(8)
+    letters = torch.tensor(list(b"ACGT"), dtype=torch.uint8, device=dev)
+    ascii = letters[torch.randint(0, 4, (n * length,), device=dev, generator=g)]
+    ends = (pair.fwd, pair.rev[::-1].translate(str.maketrans("ACGT", "TGCA")))
+    for j in range(count):
+        at = (j // 2 + 1) * length + (700, 900)[j % 2]
+        ascii[at: at + 20] = torch.tensor(list(ends[j % 2].encode()), dtype=torch.uint8, device=dev)
+    coll = _packed(ascii, n, length)
+    out = []
+    for fused in (False, True):
+        buf = path.alloc(coll, [pair], 4096, 4096, dev)
+        path.run(coll, [pair], buf, fused=fused)
+        torch.cuda.synchronize()
+        rh, ra = path.result(buf.hit_res), path.result(buf.amp_res)
+        out.append((rh, ra, path.hits_numpy(buf).tobytes(), path.amps_numpy(buf).tobytes()))
+    assert out[0][0]["count"] == count and out[0][1]["count"] == count // 2
+    assert out[0] == out[1]
