@@ -1716,7 +1716,8 @@ bool seg_mode(const ah_primer_pair* pairs, uint32_t n_pairs, uint32_t n, uint32_
 // the sites of each segment (pair, genome) together (n_sort is not written).
 ah_status launch_scan_kernel(const ScanFns& fn, Tuning tn, const ah_genomes* g, const ScanWs& w,
                              ah_result* d_res, uint64_t capacity, hipStream_t st,
-                             const ah::KeyBits* kb, const ah::SegBuffers* seg = nullptr) {
+                             const ah::KeyBits* kb, const ah::SegBuffers* seg = nullptr,
+                             bool refill = true) {
   if (g->n == 0) {
     AH_HIP(ah::launch_result_init(d_res, st));
     AH_HIP(ah::launch_zero_u64(w.cstat, 4, st));
@@ -1784,7 +1785,7 @@ ah_status launch_scan_kernel(const ScanFns& fn, Tuning tn, const ah_genomes* g, 
   uint32_t sort_grid = (uint32_t)ah::kSortGrid;
   uint32_t sort_chunk_min = ah::kSortChunkMin;
   uint32_t* seg_cnt = seg ? seg->cnt : nullptr;
-  uint32_t seg_n = seg ? seg->n_genomes : 0;
+  uint32_t seg_n = seg ? seg->n_genomes : refill ? 0 : 1;  // 1: full slices stay as they are
   void* args[] = {&words,      &nmask,      &word_off,   &len,         &tp,
                   &n,          &cands,      &slice,      &slice_cnt,   &slice_tot,
                   &slice_win,  &group_sites, &cand_sites, &slice_sites, &hist_a,
@@ -2255,6 +2256,15 @@ size_t ah_scan_workspace_bytes(const ah_genomes* g, const ah_primer_pair* pairs,
 ah_status ah_scan_primers(const ah_genomes* g, const ah_primer_pair* pairs, uint32_t n_pairs,
                           ah_hit* d_hits, uint64_t capacity, ah_result* d_res, void* d_work,
                           size_t work_bytes, void* stream) {
+  return ah::scan_primers(g, pairs, n_pairs, d_hits, capacity, d_res, d_work, work_bytes, true,
+                          stream);
+}
+
+}  // extern "C"
+
+ah_status ah::scan_primers(const ah_genomes* g, const ah_primer_pair* pairs, uint32_t n_pairs,
+                           ah_hit* d_hits, uint64_t capacity, ah_result* d_res, void* d_work,
+                           size_t work_bytes, bool refill, void* stream) {
   g_err.clear();
   ah_status s = check_genomes(g);
   if (s) return s;
@@ -2278,12 +2288,14 @@ ah_status ah_scan_primers(const ah_genomes* g, const ah_primer_pair* pairs, uint
   Carver c(d_work, work_bytes);
   ScanWs w = carve_scan(c, g->n, capacity, 0);
   // the result, the records to sort (n_sort) and the candidate statistics
-  s = launch_scan_kernel(fn, tn, g, w, d_res, capacity, st, &kb);
+  s = launch_scan_kernel(fn, tn, g, w, d_res, capacity, st, &kb, nullptr, refill);
   if (s) return s;
   ProfScope prof_sort("sort", st);
   AH_HIP(ah::launch_sort_hits(w.staging, d_hits, w.n_sort, kb, w.sb, st));
   return AH_OK;
 }
+
+extern "C" {
 
 ah_status ah_scan_primers_noalloc(const ah_genomes* g, const ah_primer_pair* pairs,
                                   uint32_t n_pairs, ah_hit* d_hits, uint64_t capacity,

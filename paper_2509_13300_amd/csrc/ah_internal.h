@@ -212,6 +212,12 @@ hipError_t launch_tile_prefix_small(const uint32_t* len, uint32_t n, uint32_t ti
 size_t scan_workspace_for(uint32_t n, uint64_t window_words, const ah_primer_pair* pairs,
                           uint32_t n_pairs, uint64_t capacity);
 
+// ah_scan_primers; refill false: full candidate slices are not filled again with sites'
+// records, the call overflows (for a caller that then runs again with more room).
+ah_status scan_primers(const ah_genomes* g, const ah_primer_pair* pairs, uint32_t n_pairs,
+                       ah_hit* d_hits, uint64_t capacity, ah_result* d_res, void* d_work,
+                       size_t work_bytes, bool refill, void* stream);
+
 // Device address of the current device's scratch array
 // (AH_SCAN_SCRATCH_BYTES bytes, the workspace of ah_scan_primers_noalloc),
 // looked up on the first call on each device.

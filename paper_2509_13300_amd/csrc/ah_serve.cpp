@@ -98,6 +98,8 @@ struct Part {
   uint64_t words = 0;       // window words of its genomes
   uint32_t max_len = 1;
   uint64_t hcap = 0, acap = 0;
+  bool ran = false;                      // its sites overflowed once: full slices are now refilled
+  uint64_t first_hcap = 0;               // hcap of that run, should the larger not fit the pool
   uint64_t n_hits = 0, n_amps = 0;       // records of a done part
   uint64_t arena_off = ~0ull, arena_bytes = 0;  // their place in the host arena, or
   std::vector<ah_hit> hits;              // host copies when the arena was full
@@ -299,7 +301,10 @@ struct ah_server {
     view.len = len_v;
     view.n = n;
     view.max_len = std::max<uint32_t>(p.max_len, 1);
-    ah_status s = ah_scan_primers(&view, &j.pair, 1, hits, p.hcap, &d_res[0], scan_ws, z.scan_ws, st);
+    // a first run leaves full candidate slices as they are: a second with more room is
+    // faster than filling them again, and does that if it has to
+    ah_status s = ah::scan_primers(&view, &j.pair, 1, hits, p.hcap, &d_res[0], scan_ws, z.scan_ws,
+                                   p.ran, st);
     if (s) return s;
     s = ah_tm(&view, &j.pair, 1, &j.tm, hits, &d_res[0], p.hcap, st);
     if (s) return s;
@@ -397,7 +402,13 @@ struct ah_server {
         continue;
       }
       const uint32_t cpi = cand->redo.empty() ? (uint32_t)cand->next : cand->redo.front();
-      const uint64_t need = size_of(*cand, cpi);
+      uint64_t need = size_of(*cand, cpi);
+      Part& part = cand->parts[cpi];
+      if (need > pool.bytes() && part.first_hcap) {  // full slices asked for too much
+        part.hcap = part.first_hcap;
+        part.first_hcap = 0;
+        need = size_of(*cand, cpi);
+      }
       if (need > pool.bytes()) {
         cand->status = ah::set_error(AH_ERR_LIMIT, "a part needs %llu bytes > pool %llu",
                                      (unsigned long long)need, (unsigned long long)pool.bytes());
@@ -435,13 +446,17 @@ struct ah_server {
     if (s != AH_OK) {
       if (j->status == AH_OK) j->status = s;
     } else if (hr[0].status != AH_OK || hr[1].status != AH_OK) {
-      // the exact counts are known now: run the part again with them
-      if (hr[0].required >= 0xffffffffull) {
+      // the exact counts (of sites, or with full slices a bound) are known now: run
+      // the part again with them
+      const bool first = hr[0].status != AH_OK && !p.ran;
+      if (first) p.ran = true;
+      p.first_hcap = first ? p.hcap : 0;  // 0: these were the sites themselves
+      if (hr[0].required >= 0xffffffffull && !first) {
         if (j->status == AH_OK)
           j->status = ah::set_error(AH_ERR_LIMIT, "a part of job %llu has %llu sites",
                                     (unsigned long long)j->id,
                                     (unsigned long long)hr[0].required);
-      } else if (hr[0].required <= p.hcap && hr[1].required <= p.acap) {
+      } else if (hr[0].required <= p.hcap && hr[1].required <= p.acap && !first) {
         // a rerun with the same buffers would overflow again
         if (j->status == AH_OK)
           j->status = ah::set_error(AH_ERR_LIMIT,
@@ -451,7 +466,7 @@ struct ah_server {
                                     (unsigned long long)hr[0].required,
                                     (unsigned long long)hr[1].required);
       } else {
-        p.hcap = std::max<uint64_t>(p.hcap, hr[0].required);
+        if (hr[0].required < 0xffffffffull) p.hcap = std::max<uint64_t>(p.hcap, hr[0].required);
         p.acap = std::max<uint64_t>(p.acap, hr[1].required);
         j->redo.push_back(pi);
         j->retries++;

@@ -513,7 +513,9 @@ __device__ __forceinline__ u64 ah_wtile(u64 r, u32 b, u32 wv) {
 // filled leave it, and of the others those without a site; then that tile's words
 // and those of the later tiles are tested exactly, and records of sites alone are
 // added.  Only a slice that sites' records overfill stays full, and such a query
-// overflows with every filter.  All of it comes after the loop over the tiles: taken
+// overflows with every filter.  Without a seg_cnt, seg_n = 1 leaves full slices as they
+// are, for a caller that runs again with more room (two runs of a small part take
+// 30 us, filling its slices 256).  All of it comes after the loop over the tiles: taken
 // inside, tile by tile and only for the words that found no place, it cost every
 // program 5-15 registers, and those near 128 a wave per SIMD (one pair at k = 0-1
 // on 300 genomes: 115 us a query, 124).
@@ -529,9 +531,11 @@ __device__ __forceinline__ u32 ah_site_windows(const AhCtx& c, u32 t, u32 p) {
   const u32 L = meta.x & 0xffu, k = meta.x >> 8;
   u32 out = ~ah_valid(c, t, L);
   u32 n[6] = {0u, 0u, 0u, 0u, 0u, 0u};  // bit b of n[i]: bit i of window b's count, at most 32
+  uint2 next = c.gw[t];  // a position ahead: few waves are left to hide loads (308 us a query, 256)
 #pragma unroll 1
   for (u32 j = 0; j < L; ++j) {  // t < S and j <= 31: in the genome's words and halo
-    const uint2 v = c.gw[t + j];
+    const uint2 v = next;
+    next = c.gw[t + min(j + 1u, L - 1u)];
     const u32 sa = 0u - ((set.x >> j) & 1u), sc = 0u - ((set.y >> j) & 1u),
               sg = 0u - ((set.z >> j) & 1u), st = 0u - ((set.w >> j) & 1u);
     u32 x = ~((~(v.x | v.y) & sa) | (~v.x & v.y & sc) | (v.x & ~v.y & sg) | (v.x & v.y & st));
@@ -763,7 +767,7 @@ extern "C" __global__ __launch_bounds__(AH_BLOCK) void ah_scan_kernel(
     cur = nx;
   }
 #if AH_REFILL
-  if (cnt > slice)
+  if (cnt > slice && (seg_cnt || seg_n == 0u))
     cnt = ah_wrefill(words, nmask, word_off, len, tile_prefix, n_genomes, k, wv, lane, s, cnt);
 #endif
   // the exact count of this wave's candidates (records written by its own
@@ -835,7 +839,7 @@ extern "C" __global__ __launch_bounds__(AH_BLOCK) void ah_scan_kernel(
     __syncthreads();                // nobody reads the tile any more
   }
 #if AH_REFILL
-  if (ah_n_cand > slice)  // the same in every thread, after the tile's barrier
+  if (ah_n_cand > slice && (seg_cnt || seg_n == 0u))  // the same in every thread, after the tile's barrier
     ah_refill(words, nmask, word_off, len, tile_prefix, n_genomes, k);
 #endif
 #if AH_TILE_COUNT
