@@ -1065,8 +1065,8 @@ extern "C" __global__ __launch_bounds__(AH_BLOCK) void ah_emit_kernel(
 // on seg_fill[segment] (cleared before the filter).  The order inside a segment
 // is left to the sort that follows.  The last workgroup also writes the segments'
 // first slots (seg_off, n_seg + 1 entries) and the tail's tiles (T sites, T
-// from the count: one tile up to 16 sites, else at most a thousand, as small as that
-// allows and of at most t_n sites; larger where n_tiles of them would not hold every site), workgroup 0 the result
+// from the count: one tile up to 16 sites, else at most a thousand, 512 above AH_SEG_MAX
+// segments, as small as that allows and of at most t_n sites; larger where n_tiles of them would not hold every site), workgroup 0 the result
 // and the candidate-list statistics, as the slice-order emit does.
 // Nothing is written when the sites overflow the capacity.
 #define AH_SEG_MAX 4096
@@ -1129,9 +1129,13 @@ extern "C" __global__ __launch_bounds__(AH_BLOCK) void ah_emit_seg_kernel(
     // a query and four times 297, against 217.  Up to 16 sites stay in one tile, which
     // waits for none (8 sites of 16 references 34.0 us a query, 35.0 in tiles of
     // their own; over 52 queries of 2-222 sites 0.2% faster, up to 32 sites
-    // 1.1% slower, up to 64 1.4%).
+    // 1.1% slower, up to 64 1.4%).  Above AH_SEG_MAX segments, where the tail's
+    // workgroups have four waves, half as many tiles (7,500 sites on 25,000 contigs 123
+    // us a query, 138 in a thousand; 1,700 on 5,000 74 and 87; 256 tiles up to 5%
+    // slower than 512).
+    const u64 target = big ? 512u : 1024u;
     u32 sh = found <= 16u ? 4u : 0u;  // T = 2^sh
-    while ((1u << sh) < t_n && (1024ull << sh) < found) ++sh;
+    while ((1u << sh) < t_n && (target << sh) < found) ++sh;
     while (((u64)n_tiles << sh) < found) ++sh;  // more sites than n_tiles tiles of t_n hold
     const u64 nt = found ? (found + (1ull << sh) - 1) >> sh : 1;
     const u32 q0 = big ? blockIdx.x * AH_BLOCK + threadIdx.x : blockIdx.x + 1 < gridDim.x ? n_seg + 1 : threadIdx.x;
